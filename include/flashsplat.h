@@ -64,7 +64,7 @@ extern "C" {
 #define FS_RED_AUTO 0   /* library choice (currently FS_RED_LDS2SUM when A_lo != NULL, else FS_RED_LDS) */
 #define FS_RED_PLAIN 1  /* one global atomic per contributing (pixel, Gaussian) */
 #define FS_RED_LDS 2    /* per-tile pre-reduction over the tile's pixels, one atomic per (tile, Gaussian, label) */
-#define FS_RED_LDS2SUM 3 /* as FS_RED_LDS, plus the rounding error of each atomic (exact two-sum) into A_lo */
+#define FS_RED_LDS2SUM 3 /* as FS_RED_LDS, compensated: A_hi + A_lo carries the sums to about one rounding */
 #define FS_RED_DET 4     /* bit-reproducible: as FS_RED_LDS, with every label summed across the wave and each
                             partial rounded to a 64-bit fixed-point integer (units of 2^-34) and added exactly;
                             the call's totals then go into A_hi (and A_lo) once per entry */
@@ -238,10 +238,14 @@ int fs_bin_sort(fs_ctx *ctx, const fs_proj *proj, const fs_camera *cams, const f
  * masks: device uint8, views concatenated, each [H][W]. A_hi: device float32
  * [n][n_classes], ADDED INTO (the caller zeroes it once; views may be
  * processed over any number of calls). A_lo: same shape, or NULL; with
- * FS_RED_LDS2SUM it receives the exact rounding error of every addition into
- * A_hi, and the partial sums of labels that no 8x8 pixel block of a tile holds
- * in 4 or more pixels (stray, noise-like labels), which are small; the
- * accumulated result is A_hi + A_lo.
+ * FS_RED_LDS2SUM the accumulated result is A_hi + A_lo. Where n * n_classes is
+ * at most 8 times the call's pixels, the call sums in float64 totals (context
+ * workspace of n * n_classes * 8 bytes) and A_hi, A_lo receive the float
+ * nearest to each sum and the float nearest to the rest. Otherwise (and under
+ * stream capture, or without room for the totals) A_lo receives the exact
+ * rounding error of every addition into A_hi, and the partial sums of labels
+ * that no 8x8 pixel block of a tile holds in 4 or more pixels (stray,
+ * noise-like labels), which are small.
  * FS_RED_DET: the call's weights are summed exactly as 64-bit fixed-point
  * integers in units of 2^-34 (each wave's float sum per (Gaussian, label) is
  * rounded once to that grid, about 3e-11), in a context workspace of

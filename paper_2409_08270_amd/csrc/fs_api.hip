@@ -246,7 +246,7 @@ ProjParams proj_params(const fs_params *p)
     return q;
 }
 
-AccParams acc_params(const fs_params *p, int32_t reduction)
+AccParams acc_params(const fs_params *p, int32_t reduction, bool wide = false)
 {
     AccParams ap;
     const double LOG2E = 1.4426950408889634;
@@ -261,6 +261,7 @@ AccParams acc_params(const fs_params *p, int32_t reduction)
     ap.count = p->count_ops ? 1 : 0;
     ap.batch = p->lds_batch ? p->lds_batch : 256;
     ap.persistent = p->persistent;
+    ap.wide = wide ? 1 : 0;
     return ap;
 }
 
@@ -451,6 +452,13 @@ __global__ void k_xcd_items(uint32_t *items, uint32_t n_tiles)
     const uint32_t base = n_tiles / kXcds, rem = n_tiles % kXcds, x = b % kXcds;
     items[b] = x * base + min(x, rem) + b / kXcds;
 }
+
+// FS_RED_LDS2SUM with float64 totals: one 64-bit atomic per (tile, Gaussian, label)
+// instead of a returning one into A_hi and one into A_lo, for a pass over the
+// n x E totals before and after. The line: a solve of 3M Gaussians x 64 classes
+// from 12 views of 1297x840 (n x E = 15 times the pixels) takes 28.9 ms either
+// way; one of 1M x 17 from 40 views (0.6 times) 17.4 against 20.3 ms.
+bool wide_pays(int64_t words, uint64_t pixels) { return (uint64_t)words <= 8 * pixels; }
 
 // FS_RED_DET: pixels per call (per scene in a batch); see to_fix's range
 constexpr uint64_t kFixMaxPixels = (uint64_t)1 << 29;
@@ -758,6 +766,16 @@ int fs_accumulate(fs_ctx *ctx, const fs_proj *proj, const fs_bins *bins, const f
         HIPCHECK(ctx, launch_fill_u32(ctx->stream, (uint32_t *)ctx->fix.p, 0u, 2 * n_fix));
         sc[0].A_fix = (unsigned long long *)ctx->fix.p;
     }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIPCHECK(ctx, hipStreamIsCapturing(ctx->stream, &cap));
+    // float64 totals, unless the call is being captured (their workspace may have to
+    // grow) or there is no room for them
+    const bool wide = reduction == FS_RED_LDS2SUM && cap == hipStreamCaptureStatusNone && wide_pays(n_fix, pl.pixels) &&
+                      ensure(ctx, ctx->fix, (size_t)n_fix * 8) == FS_OK;
+    if (wide) {
+        HIPCHECK(ctx, launch_fill_u32(ctx->stream, (uint32_t *)ctx->fix.p, 0u, 2 * n_fix));
+        sc[0].A_fix = (unsigned long long *)ctx->fix.p;
+    }
     RCHECK(upload_vec(ctx, ctx->views, pl.views));
     RCHECK(upload_vec(ctx, ctx->scenes, sc));
     const uint32_t *items = nullptr;
@@ -781,18 +799,18 @@ int fs_accumulate(fs_ctx *ctx, const fs_proj *proj, const fs_bins *bins, const f
         items = (const uint32_t *)ctx->items.p;
     }
     // events around the compositing launch alone (not under stream capture)
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIPCHECK(ctx, hipStreamIsCapturing(ctx->stream, &cap));
     const bool timed = cap == hipStreamCaptureStatusNone;
     if (timed) HIPCHECK(ctx, hipEventRecord(ctx->acc_ev[0], ctx->stream));
     HIPCHECK(ctx, launch_accumulate(ctx->stream, proj->rec, bins->vals, bins->ranges, (const ViewDev *)ctx->views.p, V,
-                                    (const SceneDev *)ctx->scenes.p, items, (uint32_t)pl.tiles, acc_params(p, reduction),
+                                    (const SceneDev *)ctx->scenes.p, items, (uint32_t)pl.tiles,
+                                    acc_params(p, reduction, wide),
                                     pix ? pix->t_final : nullptr, pix ? pix->n_blend : nullptr, nullptr, nullptr, 1,
                                     ctx->status_dev, ctx->npairs_dev + kQueueWord));
     if (timed) HIPCHECK(ctx, hipEventRecord(ctx->acc_ev[1], ctx->stream));
     ctx->acc_timed = timed;
     if (reduction == FS_RED_DET)
         HIPCHECK(ctx, launch_fix_finish(ctx->stream, (const unsigned long long *)ctx->fix.p, A_hi, A_lo, n_fix));
+    if (wide) HIPCHECK(ctx, launch_wide_finish(ctx->stream, (const double *)ctx->fix.p, A_hi, A_lo, n_fix, 1));
     return FS_OK;
 }
 
@@ -887,7 +905,9 @@ int fs_assign(fs_ctx *ctx, const float *A_hi, const float *A_lo, int64_t n, int3
     if (n_classes < 2 || n_classes > 256) return set_err(ctx, FS_ERR_ARG, "n_classes %d not in [2, 256]", n_classes);
     if (!finite_f(gamma) || gamma < -1.f || gamma > 1.f) return set_err(ctx, FS_ERR_ARG, "gamma must be finite in [-1, 1]");
     if (n > 0 && (!A_hi || !S)) return set_err(ctx, FS_ERR_ARG, "A_hi or S is NULL");
-    HIPCHECK(ctx, launch_assign(ctx->stream, A_hi, A_lo, n, n_classes, gamma, S, margin, ctx->status_dev));
+    // the kernel only writes A when it is given float64 totals
+    HIPCHECK(ctx, launch_assign(ctx->stream, const_cast<float *>(A_hi), const_cast<float *>(A_lo), n, n_classes, gamma, S,
+                                margin, ctx->status_dev));
     return FS_OK;
 }
 
@@ -1079,7 +1099,7 @@ struct SceneIn {
     const uint8_t *masks;
     int32_t E;
     float *A_hi, *A_lo;
-    unsigned long long *fix = nullptr;  // FS_RED_DET: this scene's fixed-point totals
+    unsigned long long *fix = nullptr;  // this scene's 64-bit totals (FS_RED_DET: fixed-point; wide: float64)
     uint8_t *S;
     float *margin;
     float gamma;
@@ -1128,8 +1148,9 @@ struct fs_batch {
     std::vector<SceneIn> scenes;
     std::vector<Chunk> chunks;
     DevBuf scenes_d;
-    DevBuf fix;              // FS_RED_DET: every scene's fixed-point totals
+    DevBuf fix;              // every scene's 64-bit totals (FS_RED_DET: fixed-point; wide: float64)
     int64_t fix_words = 0;
+    bool wide = false;       // the compositing adds into float64 totals (wide_pays)
     std::vector<Work> work;  // one per lane
     hipEvent_t fork = nullptr;
     DevBuf npairs;
@@ -1293,7 +1314,7 @@ int enqueue_slabs(fs_batch *b, Work &w, Chunk &c, int chunk_idx, hipStream_t s, 
         if (ev) HIPCHECK(ctx, hipEventRecord(ev[0], s));
         HIPCHECK(ctx, launch_accumulate(s, (const float *)w.rec.p, pv, (const uint32_t *)w.ranges.p,
                                         (const ViewDev *)c.views.p, V, (const SceneDev *)b->scenes_d.p, items,
-                                        (uint32_t)pl.tiles, acc_params(&b->p, b->o.reduction), nullptr, nullptr,
+                                        (uint32_t)pl.tiles, acc_params(&b->p, b->o.reduction, b->wide), nullptr, nullptr,
                                         tstate, done, k == 0 ? 1 : 0,
                                         ctx->status_dev, (uint32_t *)w.queue.p));
         if (ev) HIPCHECK(ctx, hipEventRecord(ev[1], s));
@@ -1305,14 +1326,14 @@ int enqueue_slabs(fs_batch *b, Work &w, Chunk &c, int chunk_idx, hipStream_t s, 
 int enqueue_run(fs_batch *b, hipStream_t s)
 {
     fs_ctx *ctx = b->ctx;
-    if (b->o.zero_accumulators) {
+    if (b->o.zero_accumulators && !b->wide) {  // the float64 totals replace A at the end
         for (const SceneIn &sc : b->scenes) {
             const int64_t cnt = (int64_t)sc.g.n * sc.E;
             HIPCHECK(ctx, launch_fill_u32(s, (uint32_t *)sc.A_hi, 0u, cnt));
             if (sc.A_lo) HIPCHECK(ctx, launch_fill_u32(s, (uint32_t *)sc.A_lo, 0u, cnt));
         }
     }
-    if (b->o.reduction == FS_RED_DET && b->fix_words > 0)
+    if (b->fix_words > 0)
         HIPCHECK(ctx, launch_fill_u32(s, (uint32_t *)b->fix.p, 0u, 2 * b->fix_words));
     const size_t L = b->work.size();
     if (L > 1) {
@@ -1336,9 +1357,15 @@ int enqueue_run(fs_batch *b, hipStream_t s)
     if (b->o.reduction == FS_RED_DET)
         for (const SceneIn &sc : b->scenes)
             HIPCHECK(ctx, launch_fix_finish(s, sc.fix, sc.A_hi, sc.A_lo, (int64_t)sc.g.n * sc.E));
-    for (const SceneIn &sc : b->scenes)
+    const int32_t add = b->o.zero_accumulators ? 0 : 1;
+    for (const SceneIn &sc : b->scenes) {
+        const double *wide = b->wide ? (const double *)sc.fix : nullptr;
         if (sc.S)
-            HIPCHECK(ctx, launch_assign(s, sc.A_hi, sc.A_lo, sc.g.n, sc.E, sc.gamma, sc.S, sc.margin, ctx->status_dev));
+            HIPCHECK(ctx, launch_assign(s, sc.A_hi, sc.A_lo, sc.g.n, sc.E, sc.gamma, sc.S, sc.margin, ctx->status_dev,
+                                        wide, add));
+        else if (wide)
+            HIPCHECK(ctx, launch_wide_finish(s, wide, sc.A_hi, sc.A_lo, (int64_t)sc.g.n * sc.E, add));
+    }
     return FS_OK;
 }
 
@@ -1377,10 +1404,20 @@ int batch_build(fs_batch *b, const fs_scene *scenes, int32_t n_scenes)
         b->scenes.push_back(s);
         sd.push_back(scene_dev(&in.gauss, in.gauss.n, in.masks, in.A_hi, in.A_lo, in.n_classes));
     }
-    if (b->o.reduction == FS_RED_DET) {
-        int64_t words = 0;
-        for (const SceneIn &s : b->scenes) words += (int64_t)s.g.n * s.E;
-        RCHECK(batch_alloc(b, b->fix, (size_t)words * 8));
+    int64_t words = 0;
+    uint64_t pixels = 0;
+    for (const SceneIn &s : b->scenes) {
+        words += (int64_t)s.g.n * s.E;
+        for (const fs_camera &c : s.cams) pixels += (uint64_t)c.width * (uint64_t)c.height;
+    }
+    b->wide = b->o.reduction == FS_RED_LDS2SUM && words > 0 && wide_pays(words, pixels);
+    // without room for the float64 totals the two-sum into A_hi and A_lo does as well
+    if (b->wide && batch_alloc(b, b->fix, (size_t)words * 8) != FS_OK) {
+        (void)hipGetLastError();
+        b->wide = false;
+    }
+    if (b->o.reduction == FS_RED_DET) RCHECK(batch_alloc(b, b->fix, (size_t)words * 8));
+    if (b->o.reduction == FS_RED_DET || b->wide) {
         b->fix_words = words;
         int64_t off = 0;
         for (size_t i = 0; i < b->scenes.size(); ++i) {

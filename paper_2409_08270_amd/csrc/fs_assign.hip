@@ -22,10 +22,14 @@ namespace {
 
 constexpr int kLdsDoubles = 2080;  // staged rows, 16.25 KiB (eight blocks per CU): 32 rows of 65 doubles at E = 64
 
-__global__ __launch_bounds__(256) void k_assign(const float *__restrict__ A_hi, const float *__restrict__ A_lo,
-                                                int64_t n, int32_t E, int32_t rows_per_block, float gamma,
+// WIDE: the rows come from the float64 totals `wide`; A_hi and A_lo are written
+// (added to, with `add`) on the way, and the labels use the values they then hold.
+template <bool WIDE>
+__global__ __launch_bounds__(256) void k_assign(float *__restrict__ A_hi, float *__restrict__ A_lo, int64_t n,
+                                                int32_t E, int32_t rows_per_block, float gamma,
                                                 uint8_t *__restrict__ S, float *__restrict__ margin,
-                                                unsigned long long *__restrict__ status)
+                                                unsigned long long *__restrict__ status,
+                                                const double *__restrict__ wide, int32_t add)
 {
     __shared__ double s_a[kLdsDoubles];
     __shared__ double s_tot[256];
@@ -42,8 +46,19 @@ __global__ __launch_bounds__(256) void k_assign(const float *__restrict__ A_hi, 
         int r = tid / E, e = tid - (tid / E) * E;
         const int qd = 256 / E, qm = 256 - qd * E;
         for (int i = tid; i < R * E; i += 256) {
-            double v = (double)A_hi[base + i];
-            if (A_lo) v += (double)A_lo[base + i];
+            double v;
+            if constexpr (WIDE) {
+                v = wide[base + i];
+                if (add) v += (double)A_hi[base + i] + (double)A_lo[base + i];
+                float hi, lo;
+                wide_split(v, hi, lo);
+                A_hi[base + i] = hi;
+                A_lo[base + i] = lo;
+                v = (double)hi + (double)lo;
+            } else {
+                v = (double)A_hi[base + i];
+                if (A_lo) v += (double)A_lo[base + i];
+            }
             s_a[r * stride + e] = v;
             r += qd;
             e += qm;
@@ -101,16 +116,20 @@ __global__ __launch_bounds__(256) void k_assign(const float *__restrict__ A_hi, 
 
 }  // namespace
 
-hipError_t launch_assign(hipStream_t s, const float *A_hi, const float *A_lo, int64_t n, int32_t E, float gamma,
-                         uint8_t *S, float *margin, unsigned long long *status)
+hipError_t launch_assign(hipStream_t s, float *A_hi, float *A_lo, int64_t n, int32_t E, float gamma, uint8_t *S,
+                         float *margin, unsigned long long *status, const double *wide, int32_t add)
 {
     if (n == 0) return hipSuccess;
     int rows = kLdsDoubles / (E | 1);
     if (rows > 256) rows = 256;
     if (rows < 1) rows = 1;
     const int64_t blocks = (n + rows - 1) / rows;
-    hipLaunchKernelGGL(k_assign, dim3((unsigned)blocks), dim3(256), 0, s, A_hi, A_lo, n, E, rows, gamma, S, margin,
-                       status);
+    if (wide)
+        hipLaunchKernelGGL(k_assign<true>, dim3((unsigned)blocks), dim3(256), 0, s, A_hi, A_lo, n, E, rows, gamma, S,
+                           margin, status, wide, add);
+    else
+        hipLaunchKernelGGL(k_assign<false>, dim3((unsigned)blocks), dim3(256), 0, s, A_hi, A_lo, n, E, rows, gamma, S,
+                           margin, status, wide, add);
     return hipGetLastError();
 }
 

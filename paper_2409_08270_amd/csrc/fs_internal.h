@@ -41,7 +41,8 @@ struct SceneDev {
     const uint8_t *masks;
     float *A_hi;
     float *A_lo;          // NULL: no compensation
-    unsigned long long *A_fix;  // FS_RED_DET: the call's fixed-point sums [n][E] (else NULL)
+    unsigned long long *A_fix;  // FS_RED_DET: the call's fixed-point sums [n][E]; AccParams::wide:
+                                // its float64 sums; else NULL
     uint32_t n;
     int32_t E;
 };
@@ -255,6 +256,7 @@ struct AccParams {
     int32_t count;    // 1: count in-support evaluations and blends
     int32_t batch;    // most list entries staged per batch (32..256)
     int32_t persistent;  // 1: resident workgroups pull tiles from a device counter
+    int32_t wide;     // 1 (FS_RED_LDS2SUM only): the sums go to float64 totals in SceneDev::A_fix
 };
 
 // Resumable compositing (depth slabs): with `tstate` set, each pixel's
@@ -274,8 +276,21 @@ hipError_t launch_accumulate(hipStream_t s, const float *rec, const uint32_t *va
 // once per entry, in a fixed order of operations
 hipError_t launch_fix_finish(hipStream_t s, const unsigned long long *fix, float *A_hi, float *A_lo, int64_t count);
 
-hipError_t launch_assign(hipStream_t s, const float *A_hi, const float *A_lo, int64_t n, int32_t E, float gamma,
-                         uint8_t *S, float *margin, unsigned long long *status);
+// AccParams::wide: the float64 totals wide[i] (i < count) into A_hi and A_lo, added
+// to what they hold (add = 1) or in its place (add = 0)
+hipError_t launch_wide_finish(hipStream_t s, const double *wide, float *A_hi, float *A_lo, int64_t count, int32_t add);
+
+// a value as the float nearest to it and the float nearest to the remainder
+__device__ __forceinline__ void wide_split(double v, float &hi, float &lo)
+{
+    hi = (float)v;
+    lo = (float)(v - (double)hi);
+}
+
+// with `wide`, A_hi and A_lo are first set from the float64 totals as
+// launch_wide_finish does (add as there), in the same pass over the rows
+hipError_t launch_assign(hipStream_t s, float *A_hi, float *A_lo, int64_t n, int32_t E, float gamma, uint8_t *S,
+                         float *margin, unsigned long long *status, const double *wide = nullptr, int32_t add = 0);
 
 // novel-view masks (fs_render.hip); memb is workspace of
 // render_member_bytes(n, E, mode) bytes (one byte per group of objects and
