@@ -150,36 +150,6 @@ __device__ __forceinline__ void add_global(float *hi, float *lo, int64_t idx, fl
     if (err != 0.0f) (void)atomic_add(lo, idx, err);
 }
 
-// Can any pixel centre of columns [x0, x1] and rows [y0, y1] of the 8x8 block
-// with corner (bx, by) lie inside the ellipse p (dx + r dy)^2 + s dy^2 <= lim
-// around (u, v)? Minimum of the quadratic over that box of pixel centres: zero
-// if the mean is inside, else the least edge minimum (clamped parabola
-// vertex; on a column x the vertex is at y = -p r x / (s + p r^2), on a row y
-// at x = -r y). Conservative through the margin folded into lim; used only to
-// skip work, never to decide a weight.
-__device__ __forceinline__ bool block_hit(float u, float v, float p, float r, float s, float bx, float by, float lim,
-                                          float x0, float x1, float y0, float y1)
-{
-    const float xl = bx + x0 + 0.5f - u, xh = bx + x1 + 0.5f - u;
-    const float yl = by + y0 + 0.5f - v, yh = by + y1 + 0.5f - v;
-    if (xl <= 0.0f && xh >= 0.0f && yl <= 0.0f && yh >= 0.0f) return true;
-    const float pr = p * r;
-    const float iC = __builtin_amdgcn_rcpf(fmaf(pr, r, s));
-    auto q = [&](float x, float y) {
-        const float e = fmaf(r, y, x);
-        return fmaf(p * e, e, s * y * y);
-    };
-    float qmin = 3.4e38f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const float x = i ? xh : xl;
-        qmin = fminf(qmin, q(x, fminf(fmaxf(-(pr * x) * iC, yl), yh)));
-        const float y = i ? yh : yl;
-        qmin = fminf(qmin, q(fminf(fmaxf(-(r * y), xl), xh), y));
-    }
-    return qmin <= lim;
-}
-
 // Composites one tile (the whole workgroup); every thread calls it with the same tile.
 template <bool PIX, bool COUNT, int ACC>
 __device__ __forceinline__ void accum_tile(const uint32_t tile, const float4 *__restrict__ rec,

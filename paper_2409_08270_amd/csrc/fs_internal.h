@@ -293,7 +293,7 @@ hipError_t launch_assign(hipStream_t s, float *A_hi, float *A_lo, int64_t n, int
                          float *margin, unsigned long long *status, const double *wide = nullptr, int32_t add = 0);
 
 // novel-view masks (fs_render.hip); memb is workspace of
-// render_member_bytes(n, E, mode) bytes (one byte per group of objects and
+// render_member_bytes(n, E, mode) bytes (one word per group of objects and
 // Gaussian, rebuilt from S by the launch)
 hipError_t launch_render(hipStream_t s, const float *rec, const uint32_t *vals, const uint32_t *ranges,
                          const ViewDev *views, int32_t n_views, uint32_t n_tiles, const uint8_t *S, int64_t n,
@@ -353,6 +353,46 @@ __device__ __forceinline__ int find_view_of_tile(const ViewDev *__restrict__ vie
         if (views[mid].tile_base <= t) lo = mid; else hi = mid - 1;
     }
     return lo;
+}
+
+// Bound on d^T Sigma^-1 d beyond which an entry adds nothing: the support k^2, or
+// the ellipse on which its alpha falls to alpha_min if that is smaller (opacities
+// below about 0.35), with a margin far above the rounding of the decisions
+// themselves (lo = log2(opacity)).
+__device__ __forceinline__ float reach_limit(const AccParams &P, float lo)
+{
+    const float ln4 = 1.3862943611198906f;  // 2 / log2(e)
+    return fminf(-P.cut2, lo - P.lmin) * (ln4 * 1.015625f) + 0.01f;
+}
+
+// Can any pixel centre of columns [x0, x1] and rows [y0, y1] of the 8x8 block
+// with corner (bx, by) lie inside the ellipse p (dx + r dy)^2 + s dy^2 <= lim
+// around (u, v)? Minimum of the quadratic over that box of pixel centres: zero
+// if the mean is inside, else the least edge minimum (clamped parabola
+// vertex; on a column x the vertex is at y = -p r x / (s + p r^2), on a row y
+// at x = -r y). Conservative through the margin folded into lim; used only to
+// skip work, never to decide a weight.
+__device__ __forceinline__ bool block_hit(float u, float v, float p, float r, float s, float bx, float by, float lim,
+                                          float x0, float x1, float y0, float y1)
+{
+    const float xl = bx + x0 + 0.5f - u, xh = bx + x1 + 0.5f - u;
+    const float yl = by + y0 + 0.5f - v, yh = by + y1 + 0.5f - v;
+    if (xl <= 0.0f && xh >= 0.0f && yl <= 0.0f && yh >= 0.0f) return true;
+    const float pr = p * r;
+    const float iC = __builtin_amdgcn_rcpf(fmaf(pr, r, s));
+    auto q = [&](float x, float y) {
+        const float e = fmaf(r, y, x);
+        return fmaf(p * e, e, s * y * y);
+    };
+    float qmin = 3.4e38f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float x = i ? xh : xl;
+        qmin = fminf(qmin, q(x, fminf(fmaxf(-(pr * x) * iC, yl), yh)));
+        const float y = i ? yh : yl;
+        qmin = fminf(qmin, q(fminf(fmaxf(-(r * y), xl), xh), y));
+    }
+    return qmin <= lim;
 }
 
 }  // namespace fs

@@ -9,74 +9,87 @@
 //   depth-guided: the object with rho_e > tau of least D_e (0 if none), or
 //   argmax:       argmax over all objects (background included) of rho_e.
 //
-// One workgroup renders one tile (one pixel per thread). The objects are
-// taken kObj at a time: one walk over the tile's depth-ordered list serves all
-// of them, since a Gaussian's alpha at a pixel does not depend on the object.
-// The list is staged through LDS in batches with each entry's membership bits
-// for those objects; entries that belong to none of them are compacted away
-// with wave ballots, and every thread walks the rest, updating the
-// transmittance, alpha mask and depth sum of each object the entry belongs to
-// (a uniform loop over the entry's bits). Each object's arithmetic is the same
-// sequence of operations as compositing it alone.
+// One workgroup renders one tile; each of its four waves owns an 8x8 block of
+// pixels and works by itself, without barriers. The objects are taken kObj at a
+// time, with one walk over the tile's depth-ordered list for all of them: a lane
+// takes one of 64 list entries, reads its membership bits for those objects, and
+// only if there are any gathers the record and tests whether its support can reach
+// the box of the block's live pixels. What is left goes to LDS, and the entries of
+// each object are one ballot: a scalar loop over its bits composites them in list
+// order into that object's registers (an entry of two objects is composited in
+// each). Each object's arithmetic is the same sequence of operations as compositing
+// it alone.
 //
-// The membership bits come from one byte per (group of kObj objects,
+// What bounds it: VALU issue of the steps (about 17 instructions per entry that
+// reaches the block) and, with many objects, the walks. Having every pixel walk all
+// the tile's entries of any of 8 objects, with a barrier per 256 entries and a
+// divergent branch per object, took 13.5 ms for 8 views of 800x600 of a
+// 500k-Gaussian scene with 10 classes; this takes 1.85 ms. 16 objects a walk: with 8
+// the same scene takes 2.4 ms and 4 views of 1008x756 of 1M Gaussians with 64 classes
+// 15.1 ms against 9.1 ms; with 32 the state of the objects (three registers each)
+// leaves two waves per SIMD, 3.3 and 14.4 ms. Five waves per SIMD (96 registers, 16
+// spilled outside the steps) against four: 1.85 and 2.04 ms.
+//
+// The membership bits come from one 16-bit word per (group of kObj objects,
 // Gaussian), built from S beforehand with reads that are contiguous along the
-// Gaussians, so that staging an entry gathers one byte per group instead of
+// Gaussians, so that staging an entry gathers one word per group instead of
 // one row of S per object.
 #include "fs_internal.h"
 
 namespace fs {
 namespace {
 
-constexpr int kRBatch = 256;
-constexpr int kObj = 8;  // objects composited in one walk of a tile's list
+constexpr int kObj = 16;  // objects composited in one walk of a tile's list
+using Memb = uint16_t;    // a Gaussian's membership bits for the objects of one walk
 
 // memb[q][g], bit k: Gaussian g belongs to object e_first + kObj q + k
-__global__ void k_member_bytes(const uint8_t *__restrict__ S, int64_t n, int32_t e_first, int32_t E,
-                               uint8_t *__restrict__ memb)
+__global__ void k_member_bits(const uint8_t *__restrict__ S, int64_t n, int32_t e_first, int32_t E,
+                               Memb *__restrict__ memb)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= n) return;
     for (int q = 0, e0 = e_first; e0 < E; ++q, e0 += kObj) {
         uint32_t bits = 0;
         for (int k = 0; k < kObj && e0 + k < E; ++k) bits |= (S[(int64_t)(e0 + k) * n + g] != 0 ? 1u : 0u) << k;
-        memb[(int64_t)q * n + g] = (uint8_t)bits;
+        memb[(int64_t)q * n + g] = (Memb)bits;
     }
 }
 
-__global__ __launch_bounds__(256) void k_render(const float4 *__restrict__ rec, const uint32_t *__restrict__ vals,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) void k_render(const float4 *__restrict__ rec, const uint32_t *__restrict__ vals,
                                                 const uint2 *__restrict__ ranges, const ViewDev *__restrict__ views,
-                                                int32_t n_views, const uint8_t *__restrict__ memb, int64_t n, int32_t E,
+                                                int32_t n_views, const Memb *__restrict__ memb, int64_t n, int32_t E,
                                                 AccParams P, float tau, int32_t mode, uint8_t *__restrict__ labels,
                                                 float *__restrict__ rho_out, float *__restrict__ depth_out,
                                                 int64_t n_pixels)
 {
-    __shared__ float4 s_q[kRBatch];   // u, v, p', r (LDL^T factors, p in log2 units)
-    __shared__ float4 s_q2[kRBatch];  // c', lo, thr, z
-    __shared__ uint8_t s_member[kRBatch];  // bit k: the entry belongs to object e0 + k
-    __shared__ uint16_t s_list[kRBatch];
-    __shared__ uint32_t s_wcnt[4];
+#pragma clang fp contract(off)
+    // per wave, entry j: s_rec[2 j] = (u, v, p', r), s_rec[2 j + 1] = (s', lo, thr, z), with the
+    // LDL^T factors p, s in log2 units
+    __shared__ float4 s_rec[4][2 * 64];
 
     const uint32_t tile = blockIdx.x;
     const int view = find_view_of_tile(views, n_views, tile);
     const ViewDev &C = views[view];
     const uint32_t local = tile - C.tile_base;
     const int tx = (int)(local % (uint32_t)C.tiles_x), ty = (int)(local / (uint32_t)C.tiles_x);
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    const int x = tx * P.tile_w + tid % P.tile_w;
-    const int y = ty * P.tile_h + tid / P.tile_w;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int bpr = P.tile_w >> 3;  // 8x8 blocks per tile row
+    const int x0 = tx * P.tile_w + (w % bpr) * 8, y0 = ty * P.tile_h + (w / bpr) * 8;
+    const int x = x0 + (lane & 7), y = y0 + (lane >> 3);
     const bool inside = x < C.W && y < C.H;
     const int64_t pix = (int64_t)C.mask_off + (int64_t)y * C.W + x;
     const float pxc = (float)x + 0.5f, pyc = (float)y + 0.5f;
     const float LOG2E = 1.4426950408889634f;
     const uint2 rg = ranges[tile];
     const int64_t rec_base = (int64_t)C.elem_off;
+    float4 *const recs = s_rec[w];
+    const float a_max = fminf(P.alpha_max, 1.0f);
 
     int best = 0;
     float best_d = 3.0e38f, best_rho = -1.0f;
     const int e_first = mode == 1 ? 0 : 1;
     for (int e0 = e_first; e0 < E; e0 += kObj) {
-        const uint8_t *__restrict__ mq = memb + (int64_t)((e0 - e_first) / kObj) * n;
+        const Memb *__restrict__ mq = memb + (int64_t)((e0 - e_first) / kObj) * n;
         const int ne = min(kObj, E - e0);
         float T[kObj], rho[kObj], dz[kObj];
 #pragma unroll
@@ -85,69 +98,82 @@ __global__ __launch_bounds__(256) void k_render(const float4 *__restrict__ rec, 
             rho[k] = 0.0f;
             dz[k] = 0.0f;
         }
-        // bit k: this pixel still composites object e0 + k
+        // bit k: this pixel still composites object e0 + k; alive: the same for any pixel of the wave
         uint32_t live = inside ? ((1u << ne) - 1u) : 0u;
-        for (uint32_t base = rg.x; base < rg.y; base += kRBatch) {
-            const uint32_t cnt = min((uint32_t)kRBatch, rg.y - base);
-            __syncthreads();  // previous batch consumed
-            uint32_t mbits = 0;
-            if ((uint32_t)tid < cnt) {
-                const uint32_t g = vals[base + tid];
-                mbits = mq[g];
-                if (mbits) {
-                    const float4 r0 = rec[(rec_base + g) * 2];
-                    const float4 r1 = rec[(rec_base + g) * 2 + 1];
-                    const float lo = fmaxf(__builtin_amdgcn_logf(r1.y), -200.0f);
-                    s_q[tid] = make_float4(r0.x, r0.y, -0.5f * LOG2E * r0.z, r0.w);
-                    s_q2[tid] = make_float4(-0.5f * LOG2E * r1.x, lo, P.cut2 + lo, r1.z);
-                    s_member[tid] = (uint8_t)mbits;
+        uint32_t alive = __ballot(inside) ? ((1u << ne) - 1u) : 0u;
+        // ids are read two groups of 64 ahead, their membership bits one
+        uint32_t g1 = rg.x + lane < rg.y ? vals[rg.x + lane] : 0u;
+        uint32_t g2 = rg.x + 64u + lane < rg.y ? vals[rg.x + 64u + lane] : 0u;
+        uint32_t m1 = rg.x + lane < rg.y ? mq[g1] : 0u;
+        for (uint32_t base = rg.x; base < rg.y && alive; base += 64) {
+            const uint32_t g = g1;
+            uint32_t mbits = m1 & alive;
+            g1 = g2;
+            m1 = base + 64u + lane < rg.y ? mq[g1] : 0u;
+            if (base + 128u + lane < rg.y) g2 = vals[base + 128u + lane];
+            if (__ballot(mbits != 0u) == 0ull) continue;
+            // columns bx.. and rows by.. of the wave's live pixels (lane = 8 * row + column)
+            const unsigned long long lm = __ballot(live != 0u);
+            uint32_t cols = (uint32_t)(lm | (lm >> 32));
+            cols |= cols >> 16;
+            cols = (cols | (cols >> 8)) & 0xFFu;
+            const float bx0 = (float)(__ffs((int)cols) - 1), bx1 = (float)(31 - __clz((int)cols));
+            const float by0 = (float)((__ffsll((long long)lm) - 1) >> 3), by1 = (float)((63 - __clzll((long long)lm)) >> 3);
+            if (mbits) {
+                const float4 r0 = rec[(rec_base + g) * 2];
+                const float4 r1 = rec[(rec_base + g) * 2 + 1];
+                const float lo = fmaxf(__builtin_amdgcn_logf(r1.y), -200.0f);
+                if (block_hit(r0.x, r0.y, r0.z, r0.w, r1.x, (float)x0, (float)y0, reach_limit(P, lo), bx0, bx1, by0, by1)) {
+                    recs[2 * lane] = make_float4(r0.x, r0.y, -0.5f * LOG2E * r0.z, r0.w);
+                    recs[2 * lane + 1] = make_float4(-0.5f * LOG2E * r1.x, lo, P.cut2 + lo, r1.z);
+                } else {
+                    mbits = 0u;
                 }
             }
-            // entries of the batch that belong to any of the objects, in list order:
-            // per-wave ballots, then wave offsets
-            const unsigned long long bm = __ballot(mbits != 0u);
-            if (lane == 0) s_wcnt[w] = (uint32_t)__popcll(bm);
-            __syncthreads();
-            uint32_t before = 0, total = 0;
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t c = s_wcnt[i];
-                if (i < w) before += c;
-                total += c;
-            }
-            if (mbits) s_list[before + (uint32_t)__popcll(bm & ((1ull << lane) - 1ull))] = (uint16_t)tid;
-            __syncthreads();
-            if (live) {
-                for (uint32_t i = 0; i < total; ++i) {
-                    const uint32_t j = s_list[i];
-                    const uint32_t mem = s_member[j] & live;
-                    if (mem == 0u) continue;
-                    const float4 q = s_q[j];
-                    const float4 q2 = s_q2[j];
+            __builtin_amdgcn_wave_barrier();
+            uint32_t left = 0;  // objects with a live pixel after this group of entries
+#pragma unroll
+            for (int k = 0; k < kObj; ++k) {
+                if (!((alive >> k) & 1u)) continue;
+                unsigned long long todo = __ballot((mbits >> k) & 1u);
+                bool on = (live >> k) & 1u;
+                float Tk = T[k], rk = rho[k], dk = dz[k];
+                while (todo) {
+                    const int j = __ffsll((long long)todo) - 1;
+                    todo &= todo - 1ull;
+                    const float4 q = recs[2 * j];
+                    const float4 q2 = recs[2 * j + 1];
                     const float dx = pxc - q.x, dy = pyc - q.y;
                     const float e = fmaf(q.w, dy, dx);
                     const float pw = fmaf(q.z * e, e, fmaf(q2.x * dy, dy, q2.y));
-                    if (pw < q2.z) continue;
-                    const float alpha = fminf(P.alpha_max, __builtin_amdgcn_exp2f(pw));
-                    if (alpha < P.alpha_min) continue;
-                    // each object the entry belongs to, as if composited alone
-#pragma unroll
-                    for (int k = 0; k < kObj; ++k) {
-                        if ((mem >> k) & 1u) {
-                            const float Tn = fmaf(-T[k], alpha, T[k]);
-                            if (Tn < P.t_min) {
-                                live &= ~(1u << k);
-                            } else {
-                                const float wv = alpha * T[k];
-                                rho[k] += wv;
-                                dz[k] = fmaf(wv, q2.w, dz[k]);
-                                T[k] = Tn;
-                            }
+                    const float av = fminf(a_max, __builtin_amdgcn_exp2f(pw));
+                    // alpha = 0 leaves T, rho and the depth sum as they are
+                    const float alpha = on && pw >= q2.z && av >= P.alpha_min ? av : 0.0f;
+                    const float Tn = fmaf(-Tk, alpha, Tk);
+                    const float wv = alpha * Tk;
+                    const bool stop = alpha > 0.0f && Tn < P.t_min;  // the entry is not added, the pixel ends
+                    if (__builtin_expect(__ballot(stop) != 0ull, 0)) {
+                        if (!stop) {
+                            rk = fmaf(alpha, Tk, rk);
+                            dk = fmaf(wv, q2.w, dk);
+                            Tk = Tn;
                         }
+                        on = on && !stop;
+                        if (__ballot(on) == 0ull) break;
+                    } else {
+                        rk = fmaf(alpha, Tk, rk);
+                        dk = fmaf(wv, q2.w, dk);
+                        Tk = Tn;
                     }
-                    if (live == 0u) break;
                 }
+                T[k] = Tk;
+                rho[k] = rk;
+                dz[k] = dk;
+                live = on ? live : (live & ~(1u << k));
+                if (__ballot(on)) left |= 1u << k;
             }
-            if (__syncthreads_or(live != 0u) == 0) break;
+            alive = left;
+            __builtin_amdgcn_wave_barrier();  // the records are read before the next group's are written
         }
 #pragma unroll
         for (int k = 0; k < kObj; ++k) {
@@ -182,13 +208,13 @@ hipError_t launch_render(hipStream_t s, const float *rec, const uint32_t *vals, 
 {
     if (n_tiles == 0) return hipSuccess;
     if (n > 0) {
-        hipLaunchKernelGGL(k_member_bytes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, S, n,
-                           mode == 1 ? 0 : 1, E, memb);
+        hipLaunchKernelGGL(k_member_bits, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, S, n,
+                           mode == 1 ? 0 : 1, E, (Memb *)memb);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_render, dim3(n_tiles), dim3(256), 0, s, reinterpret_cast<const float4 *>(rec), vals,
-                       reinterpret_cast<const uint2 *>(ranges), views, n_views, memb, n, E, p, tau, mode, labels, rho,
+                       reinterpret_cast<const uint2 *>(ranges), views, n_views, (const Memb *)memb, n, E, p, tau, mode, labels, rho,
                        depth, n_pixels);
     return hipGetLastError();
 }
@@ -196,7 +222,7 @@ hipError_t launch_render(hipStream_t s, const float *rec, const uint32_t *vals, 
 int64_t render_member_bytes(int64_t n, int32_t E, int32_t mode)
 {
     const int e_first = mode == 1 ? 0 : 1;
-    return n * (int64_t)((E - e_first + kObj - 1) / kObj);
+    return (int64_t)sizeof(Memb) * n * (int64_t)((E - e_first + kObj - 1) / kObj);
 }
 
 }  // namespace fs
