@@ -9,103 +9,104 @@
 // paper calls dynamic programming), in float64 from A_hi + A_lo: o = total - a
 // is then exact to about 1e-16 of the row sum.
 //
-// Memory: A is row-major [n][E] (one row per Gaussian) and S is [E][n]. A
-// block stages a tile of rows in LDS with coalesced loads and writes S and
-// the margins column-tile by column-tile, so both sides stay coalesced. The
-// staged rows are E | 1 doubles apart: consecutive lanes read one column of
-// consecutive rows, and an even stride (E = 64: 512 bytes) would send them
-// all to the same LDS banks.
-#include "fs_internal.h"
+// Memory: row tiles of fs_rows.h. What bounds it: HBM. 3M rows of 64 classes with margins move
+// 2.5 GB in 544 us, 4.6 TB/s (a copy reaches 4.75); with one element per lane and two divisions
+// each 800 us. Smaller tiles keep eight blocks on a CU: 4160 staged doubles instead of 2304 take
+// twice as long.
+#include "fs_rows.h"
 
 namespace fs {
 namespace {
 
-constexpr int kLdsDoubles = 2080;  // staged rows, 16.25 KiB (eight blocks per CU): 32 rows of 65 doubles at E = 64
+constexpr int kLdsDoubles = 2304;  // most staged doubles: 18 KiB, eight blocks per CU
 
 // WIDE: the rows come from the float64 totals `wide`; A_hi and A_lo are written
 // (added to, with `add`) on the way, and the labels use the values they then hold.
 template <bool WIDE>
 __global__ __launch_bounds__(256) void k_assign(float *__restrict__ A_hi, float *__restrict__ A_lo, int64_t n,
-                                                int32_t E, int32_t rows_per_block, float gamma,
-                                                uint8_t *__restrict__ S, float *__restrict__ margin,
-                                                unsigned long long *__restrict__ status,
+                                                int32_t E, RowTile tl, float gamma, uint8_t *__restrict__ S,
+                                                float *__restrict__ margin, unsigned long long *__restrict__ status,
                                                 const double *__restrict__ wide, int32_t add)
 {
-    __shared__ double s_a[kLdsDoubles];
-    __shared__ double s_tot[256];
-    __shared__ uint32_t s_members[256];
+    // as large as this launch needs, for more blocks per CU
+    extern __shared__ double s_a[];
+    double *const s_tot = s_a + E * (tl.rows + 1);
+    uint32_t *const s_members = reinterpret_cast<uint32_t *>(s_tot + tl.rows);
     __shared__ uint32_t s_cnt[3];
-    const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
-    const int R = (int)min((int64_t)rows_per_block, n - r0);
-    const int tid = threadIdx.x;
+    const int64_t r0 = tile_of_block() * tl.rows;
+    const int R = (int)min((int64_t)tl.rows, n - r0);
+    const int tid = threadIdx.x, rs = tl.rows + 1;
     if (tid < 3) s_cnt[tid] = 0;
-    const int stride = E | 1;
-    // coalesced load of R rows x E columns; (r, e) of element i advance with i
-    const int64_t base = r0 * E;
-    {
-        int r = tid / E, e = tid - (tid / E) * E;
-        const int qd = 256 / E, qm = 256 - qd * E;
-        for (int i = tid; i < R * E; i += 256) {
-            double v;
-            if constexpr (WIDE) {
-                v = wide[base + i];
-                if (add) v += (double)A_hi[base + i] + (double)A_lo[base + i];
-                float hi, lo;
-                wide_split(v, hi, lo);
-                A_hi[base + i] = hi;
-                A_lo[base + i] = lo;
-                v = (double)hi + (double)lo;
+    const bool vec = aligned16(A_hi) && aligned16(A_lo) && aligned16(wide);
+    stage_rows(s_a, r0, R, E, tl, [&](int64_t i, int m, double (&v)[4]) {
+        if constexpr (WIDE) {
+            double old[4] = {0.0, 0.0, 0.0, 0.0};
+            if (add) load_a4(A_hi, A_lo, vec, i, m, old);
+            float hi[4], lo[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                wide_split(j < m ? old[j] + wide[i + j] : 0.0, hi[j], lo[j]);
+                v[j] = (double)hi[j] + (double)lo[j];
+            }
+            if (vec && m == 4) {
+                *reinterpret_cast<float4 *>(A_hi + i) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+                *reinterpret_cast<float4 *>(A_lo + i) = make_float4(lo[0], lo[1], lo[2], lo[3]);
             } else {
-                v = (double)A_hi[base + i];
-                if (A_lo) v += (double)A_lo[base + i];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (j >= m) break;
+                    A_hi[i + j] = hi[j];
+                    A_lo[i + j] = lo[j];
+                }
             }
-            s_a[r * stride + e] = v;
-            r += qd;
-            e += qm;
-            if (e >= E) {
-                e -= E;
-                ++r;
-            }
+        } else {
+            load_a4(A_hi, A_lo, vec, i, m, v);
         }
-    }
-    __syncthreads();
-    if (tid < R) {
-        double tot = 0.0;
-        // in order e = 0, 1, ...; unrolled so that several LDS reads are in flight
-#pragma unroll 8
-        for (int e = 0; e < E; ++e) tot += s_a[tid * stride + e];
+    });
+    if (tid < tl.rows) {
+        const double tot = row_total(s_a, tid, E, tl);
         s_tot[tid] = tot;
         s_members[tid] = 0;
-        if (tot == 0.0) atomicAdd(&s_cnt[0], 1u);
+        const int r = ((tid & ((1 << tl.gsh) - 1)) << 2) + (tid >> tl.gsh);  // the row at position tid
+        if (tot == 0.0 && r < R) atomicAdd(&s_cnt[0], 1u);
     }
     __syncthreads();
     const double gd = (double)gamma;
     uint32_t low = 0;
-    // element i = t * R + r (object t, row r); (t, r) advance with i
-    int t = tid / R, r = tid - (tid / R) * R;
-    const int qd = 256 / R, qm = 256 - qd * R;
-    for (int i = tid; i < R * E; i += 256) {
-        const double a = s_a[r * stride + t];
-        double o = s_tot[r] - a;
-        if (o < 0.0) o = 0.0;
-        const double s = fmax(a + o, 1e-12);
-        const double an = a / s, on = o / s;
-        const bool in = an > on + gd;
-        const double m = fabs(an - on - gd);
-        S[(int64_t)t * n + r0 + r] = in ? 1 : 0;
-        if (margin) margin[(int64_t)t * n + r0 + r] = (float)m;
-        if (in) atomicAdd(&s_members[r], 1u);
-        if (m < 1e-4) low++;
-        t += qd;
-        r += qm;
-        if (r >= R) {
-            r -= R;
-            ++t;
+    for (int i = tid; i < E << tl.gsh; i += 256) {
+        const int t = i >> tl.gsh, g = i & ((1 << tl.gsh) - 1);
+        const int left = R - 4 * g;  // valid rows from this thread's first
+        if (left <= 0) continue;
+        uint32_t lab = 0;
+        float m4[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int pos = (j << tl.gsh) + g;
+            double an, on;
+            normalise(s_a[t * rs + pos], s_tot[pos], an, on);
+            const bool in = j < left && an > on + gd;
+            const double m = fabs(an - on - gd);
+            lab |= (in ? 1u : 0u) << (8 * j);
+            m4[j] = (float)m;
+            if (in) atomicAdd(&s_members[pos], 1u);
+            if (j < left && m < 1e-4) low++;
+        }
+        const int64_t o = (int64_t)t * n + r0 + 4 * g;
+        if (left >= 4) {
+            store_bytes4(S + o, lab);
+            if (margin) store_floats4(margin + o, make_float4(m4[0], m4[1], m4[2], m4[3]));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (j >= left) break;
+                S[o + j] = (uint8_t)(lab >> (8 * j));
+                if (margin) margin[o + j] = m4[j];
+            }
         }
     }
     if (low) atomicAdd(&s_cnt[2], low);
     __syncthreads();
-    if (tid < R && s_members[tid] > 1) atomicAdd(&s_cnt[1], 1u);
+    if (tid < tl.rows && s_members[tid] > 1) atomicAdd(&s_cnt[1], 1u);
     __syncthreads();
     if (tid == 0) {
         if (s_cnt[0]) status_add(status, ST_UNSEEN, (unsigned long long)s_cnt[0]);
@@ -120,15 +121,14 @@ hipError_t launch_assign(hipStream_t s, float *A_hi, float *A_lo, int64_t n, int
                          float *margin, unsigned long long *status, const double *wide, int32_t add)
 {
     if (n == 0) return hipSuccess;
-    int rows = kLdsDoubles / (E | 1);
-    if (rows > 256) rows = 256;
-    if (rows < 1) rows = 1;
-    const int64_t blocks = (n + rows - 1) / rows;
+    const RowTile tl = row_tile(E, kLdsDoubles);
+    const int64_t blocks = (n + tl.rows - 1) / tl.rows;
+    const size_t lds = (size_t)E * (tl.rows + 1) * 8 + (size_t)tl.rows * 12;
     if (wide)
-        hipLaunchKernelGGL(k_assign<true>, dim3((unsigned)blocks), dim3(256), 0, s, A_hi, A_lo, n, E, rows, gamma, S,
+        hipLaunchKernelGGL(k_assign<true>, dim3((unsigned)blocks), dim3(256), lds, s, A_hi, A_lo, n, E, tl, gamma, S,
                            margin, status, wide, add);
     else
-        hipLaunchKernelGGL(k_assign<false>, dim3((unsigned)blocks), dim3(256), 0, s, A_hi, A_lo, n, E, rows, gamma, S,
+        hipLaunchKernelGGL(k_assign<false>, dim3((unsigned)blocks), dim3(256), lds, s, A_hi, A_lo, n, E, tl, gamma, S,
                            margin, status, wide, add);
     return hipGetLastError();
 }
