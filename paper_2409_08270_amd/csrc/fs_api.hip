@@ -991,8 +991,8 @@ int fs_prompt_propagate(fs_ctx *ctx, const fs_gaussians *g, const fs_camera *cam
     Plan pl;
     plan_add(pl, p, 0, g->n, cams, 0, n_views, 0);
     RCHECK(upload_vec(ctx, ctx->views, pl.views));
-    int64_t blocks = (g->n + 255) / 256;
-    if (blocks > 512) blocks = 512;
+    // blocks per prompt: 4 or more centres per lane, and about 1024 blocks in all
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((g->n + 1023) / 1024, std::max<int64_t>(16, 1024 / n_prompts)));
     // device layout: prompts | ids [P][1+k] | uv [P][V][2] | visible [P][V]
     const size_t in_bytes = P * 3 * sizeof(float);
     const size_t ids_off = (in_bytes + 255) & ~(size_t)255;
