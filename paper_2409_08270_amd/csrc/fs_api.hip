@@ -283,12 +283,13 @@ struct Plan {
     uint64_t elems = 0;
     uint64_t tiles = 0;
     uint64_t pixels = 0;
+    uint64_t sat = 0;          // entries of the live-tile tables
 };
 
 // Device description of one view: camera, tile grid, and where its tiles,
 // mask, projection plane and pixel state start.
 ViewDev make_view(const fs_camera &c, const fs_params *p, uint32_t scene, int64_t n, uint64_t tile_base,
-                  uint64_t mask_off, uint64_t elem_off, uint64_t pix_off)
+                  uint64_t mask_off, uint64_t elem_off, uint64_t pix_off, uint64_t sat_off = 0)
 {
     ViewDev d;
     memcpy(d.R, c.R, sizeof(d.R));
@@ -302,6 +303,7 @@ ViewDev make_view(const fs_camera &c, const fs_params *p, uint32_t scene, int64_
     d.mask_off = mask_off;
     d.elem_off = elem_off;
     d.pix_off = pix_off;
+    d.sat_off = sat_off;
     d.n = (uint32_t)n;
     d.pad = 0;
     {
@@ -322,7 +324,7 @@ void plan_add(Plan &pl, const fs_params *p, uint32_t scene, int64_t n, const fs_
     const int first = (int)pl.views.size();
     for (int v = v0; v < v1; ++v) {
         const fs_camera &c = cams[v];
-        const ViewDev d = make_view(c, p, scene, n, pl.tiles, moff, pl.elems, pl.pixels);
+        const ViewDev d = make_view(c, p, scene, n, pl.tiles, moff, pl.elems, pl.pixels, pl.sat);
         pl.views.push_back(d);
         SegDev sg;
         sg.off = pl.elems;
@@ -334,6 +336,7 @@ void plan_add(Plan &pl, const fs_params *p, uint32_t scene, int64_t n, const fs_
         pl.dblocks += (uint32_t)((n + kSortTile - 1) / kSortTile);
         pl.elems += (uint64_t)n;
         pl.tiles += (uint64_t)d.tiles_x * d.tiles_y;
+        pl.sat += (uint64_t)(d.tiles_x + 1) * (uint64_t)(d.tiles_y + 1);
         pl.pixels += (uint64_t)c.width * c.height;
         moff += (uint64_t)c.width * c.height;
     }
@@ -739,9 +742,8 @@ int fs_bin_sort(fs_ctx *ctx, const fs_proj *proj, const fs_camera *cams, const f
         k0 = (uint32_t *)ctx->pk_alt.p; v0 = (uint32_t *)ctx->pv_alt.p; k1 = out->tiles; v1 = out->vals;
     }
     HIPCHECK(ctx, launch_emit(s, dk, dv, (const uint32_t *)ctx->offsets.p, (const uint32_t *)ctx->counts.p, proj->rec,
-                              proj->rect, p->fp64_conic ? nullptr : proj->flags, views, V, total,
-                              (uint32_t)out->capacity, p->tile_w, p->tile_h,
-                              p->sigma_k, nullptr, k0, v0, ctx->status_dev));
+                              proj->rect, views, V, total, (uint32_t)out->capacity, p->tile_w, p->tile_h, p->sigma_k,
+                              nullptr, nullptr, k0, v0, ctx->status_dev));
     // without a host count, the device count caps the sort (entries past it are never read)
     HIPCHECK(ctx, radix_sort(s, k0, v0, k1, v1, (const SegDev *)ctx->psegs.p, 1, pblocks, passes * 8, ctx->sort_ws.p,
                              n_pairs ? nullptr : ctx->npairs_dev, ptpb));
@@ -1137,7 +1139,7 @@ struct Chunk {
 struct Work {
     DevBuf rec, rect, ntiles, flags, codes, dkeys, dvals, dkeys2, dvals2, counts, offsets;
     DevBuf ptiles, pvals, pk_alt, pv_alt, ranges, items, items_k, items_k2, items_v2;
-    DevBuf sort_ws, scan_ws, tscan_ws, view_offs, tstate, tile_done, queue;
+    DevBuf sort_ws, scan_ws, tscan_ws, view_offs, tstate, tile_done, live_table, queue;
     hipStream_t stream = nullptr;  // default priority, created with the batch (lanes > 1)
     hipEvent_t done = nullptr;
 };
@@ -1155,7 +1157,7 @@ struct fs_batch {
     std::vector<Work> work;  // one per lane
     hipEvent_t fork = nullptr;
     DevBuf npairs;
-    uint64_t max_elems = 0, max_tiles = 0, max_pairs = 0, max_pixels = 0;
+    uint64_t max_elems = 0, max_tiles = 0, max_pairs = 0, max_pixels = 0, max_sat = 0;
     int n_slabs = 1;
     uint32_t slab_num[9] = {0, 1024};  // depth-slab boundaries, numerators over 1024
     uint32_t max_dblocks = 0, max_pblocks = 0, max_lblocks = 0;
@@ -1177,7 +1179,7 @@ std::vector<DevBuf *> batch_bufs(fs_batch *b)
         for (DevBuf *d : {&w.rec, &w.rect, &w.ntiles, &w.flags, &w.codes, &w.dkeys, &w.dvals, &w.dkeys2, &w.dvals2,
                           &w.counts, &w.offsets, &w.ptiles, &w.pvals, &w.pk_alt, &w.pv_alt, &w.ranges, &w.items, &w.items_k,
                           &w.items_k2, &w.items_v2, &w.sort_ws, &w.scan_ws, &w.tscan_ws, &w.view_offs, &w.tstate,
-                          &w.tile_done, &w.queue})
+                          &w.tile_done, &w.live_table, &w.queue})
             v.push_back(d);
     for (Chunk &c : b->chunks) {
         v.push_back(&c.views);
@@ -1267,15 +1269,16 @@ int enqueue_slabs(fs_batch *b, Work &w, Chunk &c, int chunk_idx, hipStream_t s, 
     for (int k = 0; k < S; ++k) {
         uint32_t *np = (uint32_t *)b->npairs.p + (size_t)chunk_idx * S + k;
         const Slab sl{b->slab_num[k], b->slab_num[k + 1]};
+        // the first slab has no finished tile yet
+        const uint8_t *dn = k > 0 ? done : nullptr;
+        uint32_t *table = (uint32_t *)w.live_table.p;
+        if (dn) HIPCHECK(ctx, launch_live_table(s, (const ViewDev *)c.views.p, V, dn, table));
         HIPCHECK(ctx, launch_slab_counts(s, dk, dv, (const float *)w.rec.p, (const int16_t *)w.rect.p,
-                                         b->p.fp64_conic ? nullptr : (const uint8_t *)w.flags.p,
-                                         (const int32_t *)w.ntiles.p,
-                                         (const ViewDev *)c.views.p, V, total, sl, k > 0 ? done : nullptr,
+                                         (const int32_t *)w.ntiles.p, (const ViewDev *)c.views.p, V, total, sl, dn, table,
                                          b->p.tile_w, b->p.tile_h, b->p.sigma_k, (const uint64_t *)w.codes.p,
                                          (uint32_t *)w.counts.p, c.cshift));
         HIPCHECK(ctx, scan_exclusive(s, (const uint32_t *)w.counts.p, (uint32_t *)w.offsets.p, total, np,
                                      w.scan_ws.p));
-        const uint8_t *fl = b->p.fp64_conic ? nullptr : (const uint8_t *)w.flags.p;
         // tile lists: the sort's last pass counts the pairs of every tile (and
         // skips writing the sorted tile ids, which nothing reads), then the
         // ranges are the exclusive scan of those counts
@@ -1284,9 +1287,9 @@ int enqueue_slabs(fs_batch *b, Work &w, Chunk &c, int chunk_idx, hipStream_t s, 
         if (c.packed) {
             // one u32 item per pair, sorted per view by its tile bits only
             HIPCHECK(ctx, launch_emit(s, dk, dv, (const uint32_t *)w.offsets.p, (const uint32_t *)w.counts.p,
-                                      (const float *)w.rec.p, (const int16_t *)w.rect.p, fl,
+                                      (const float *)w.rec.p, (const int16_t *)w.rect.p,
                                       (const ViewDev *)c.views.p, V, total, c.pair_cap, b->p.tile_w, b->p.tile_h,
-                                      b->p.sigma_k, k > 0 ? done : nullptr, pt, nullptr, ctx->status_dev, c.gbits,
+                                      b->p.sigma_k, dn, table, pt, nullptr, ctx->status_dev, c.gbits,
                                       (const uint64_t *)w.codes.p, c.cshift));
             HIPCHECK(ctx, launch_pair_segs(s, (const uint32_t *)w.offsets.p, (const ViewDev *)c.views.p, V, total, np,
                                            c.pair_cap, (SegDev *)c.psegs.p, ctx->status_dev));
@@ -1294,9 +1297,9 @@ int enqueue_slabs(fs_batch *b, Work &w, Chunk &c, int chunk_idx, hipStream_t s, 
                                             w.sort_ws.p, c.ptpb, tcount));
         } else {
             HIPCHECK(ctx, launch_emit(s, dk, dv, (const uint32_t *)w.offsets.p, (const uint32_t *)w.counts.p,
-                                      (const float *)w.rec.p, (const int16_t *)w.rect.p, fl,
+                                      (const float *)w.rec.p, (const int16_t *)w.rect.p,
                                       (const ViewDev *)c.views.p, V, total, c.pair_cap, b->p.tile_w, b->p.tile_h,
-                                      b->p.sigma_k, k > 0 ? done : nullptr, k0, v0, ctx->status_dev, 0,
+                                      b->p.sigma_k, dn, table, k0, v0, ctx->status_dev, 0,
                                       (const uint64_t *)w.codes.p, c.cshift));
             HIPCHECK(ctx, radix_sort(s, k0, v0, k1, v1, (const SegDev *)c.psegs.p, 1, c.pblocks, c.passes * 8,
                                      w.sort_ws.p, np, c.ptpb, tcount, false));
@@ -1581,6 +1584,7 @@ int batch_build(fs_batch *b, const fs_scene *scenes, int32_t n_scenes)
         b->max_pairs = std::max<uint64_t>(b->max_pairs, c.slab_max);
         b->max_tiles = std::max<uint64_t>(b->max_tiles, c.plan.tiles);
         b->max_pixels = std::max<uint64_t>(b->max_pixels, c.plan.pixels);
+        b->max_sat = std::max<uint64_t>(b->max_sat, c.plan.sat);
         b->max_elems = std::max<uint64_t>(b->max_elems, c.plan.elems);
         b->max_dblocks = std::max(b->max_dblocks, c.plan.dblocks);
         b->total_pairs += (int64_t)c.pairs;
@@ -1655,6 +1659,7 @@ int batch_build(fs_batch *b, const fs_scene *scenes, int32_t n_scenes)
         if (S > 1) {
             RCHECK(batch_alloc(b, w.tstate, (size_t)std::max<uint64_t>(b->max_pixels, 1) * 4));
             RCHECK(batch_alloc(b, w.tile_done, ((size_t)b->max_tiles + 3) / 4 * 4 + 4));
+            RCHECK(batch_alloc(b, w.live_table, (size_t)b->max_sat * 4));
         }
     }
     if (n_lanes > 1) {

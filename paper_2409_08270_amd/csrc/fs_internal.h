@@ -31,6 +31,7 @@ struct ViewDev {
     uint64_t mask_off;    // offset of this view's mask inside its scene's masks
     uint64_t elem_off;    // first element of this view's projection plane
     uint64_t pix_off;     // first pixel of this view in the call's per-pixel state buffer
+    uint64_t sat_off;     // first entry of this view's table of live tiles, (tiles_x + 1) x (tiles_y + 1)
     uint32_t n;           // Gaussians in the scene (= plane length)
     uint32_t pad;
     float limx, limy;     // guard-band limits of x/z, y/z: guard * ((0.5 W) / fx), likewise for y
@@ -199,31 +200,32 @@ struct Slab {
     uint32_t num_lo, num_hi;
 };
 
+// Summed-area tables (at views[v].sat_off) of every view's tiles that are not marked in `done`.
+hipError_t launch_live_table(hipStream_t s, const ViewDev *views, int32_t n_views, const uint8_t *done, uint32_t *table);
+
 // counts[i] = listed tiles of depth-sorted element i that lie in the slab and
-// whose tile is not marked in `done` (NULL: no tile is done); 0 outside the slab.
-// `flags` may be NULL when float64 conics are on: rec's float64 mark then
-// gives the degenerate flag, and one gather per element is saved. `codes` as
-// for launch_emit.
+// whose tile is not marked in `done` (NULL: no tile is done; else `table` holds its
+// live-tile tables); 0 outside the slab. `codes` as for launch_emit.
 hipError_t launch_slab_counts(hipStream_t s, const uint32_t *sorted_keys, const uint32_t *sorted_vals,
-                              const float *rec, const int16_t *rect, const uint8_t *flags, const int32_t *ntiles,
-                              const ViewDev *views, int32_t n_views, int64_t total, Slab slab, const uint8_t *done,
-                              int32_t tile_w, int32_t tile_h, float sigma_k, const uint64_t *codes,
-                              uint32_t *counts, int32_t cshift = 0);
+                              const float *rec, const int16_t *rect, const int32_t *ntiles, const ViewDev *views,
+                              int32_t n_views, int64_t total, Slab slab, const uint8_t *done, const uint32_t *table,
+                              int32_t tile_w, int32_t tile_h, float sigma_k, const uint64_t *codes, uint32_t *counts,
+                              int32_t cshift = 0);
 
 // emits, for every depth-sorted element, one (tile, id) pair per listed tile
 // (the row_span rule) at offsets[i]; pairs at or beyond `capacity` are
 // dropped and latched
-// (tiles marked in `done`, if not NULL, are skipped, as in launch_slab_counts;
-// `flags` may be NULL as there). With gbits > 0 each pair is one packed item
+// (tiles marked in `done`, if not NULL, are skipped, as in launch_slab_counts).
+// With gbits > 0 each pair is one packed item
 // (tile index within its view << gbits) | Gaussian id in tiles_out, and
 // vals_out is not used. `codes` (may be NULL) are the projection's emission
 // records (span code and rectangle); elements with a code skip the row_span
 // recomputation, and the rectangle is read from the record, not from `rect`.
 hipError_t launch_emit(hipStream_t s, const uint32_t *sorted_keys, const uint32_t *sorted_vals,
                        const uint32_t *offsets, const uint32_t *counts, const float *rec, const int16_t *rect,
-                       const uint8_t *flags, const ViewDev *views, int32_t n_views, int64_t total,
-                       uint32_t capacity, int32_t tile_w, int32_t tile_h, float sigma_k, const uint8_t *done,
-                       uint32_t *tiles_out, uint32_t *vals_out, unsigned long long *status, int32_t gbits = 0,
+                       const ViewDev *views, int32_t n_views, int64_t total, uint32_t capacity, int32_t tile_w,
+                       int32_t tile_h, float sigma_k, const uint8_t *done, const uint32_t *table, uint32_t *tiles_out,
+                       uint32_t *vals_out, unsigned long long *status, int32_t gbits = 0,
                        const uint64_t *codes = nullptr, int32_t cshift = 0);
 
 // ranges[t] = [starts[t], starts[t] + counts[t]), or [0, 0) if counts[t] == 0

@@ -420,11 +420,8 @@ __device__ __forceinline__ bool in_slab(const ViewDev &C, int64_t i, Slab sl)
 }
 
 __global__ void k_slab_counts(const uint32_t *__restrict__ skeys, const uint32_t *__restrict__ svals,
-                              const float4 *__restrict__ rec, const short4 *__restrict__ rect,
-                              const uint8_t *__restrict__ flags, const int32_t *__restrict__ ntiles,
-                              const ViewDev *__restrict__ views, int32_t n_views, int64_t total, Slab sl,
-                              const uint8_t *__restrict__ done, int32_t tw, int32_t th, float sigma_k,
-                              const ulonglong2 *__restrict__ codes, uint32_t *__restrict__ counts, int32_t cshift)
+                              const int32_t *__restrict__ ntiles, const ViewDev *__restrict__ views, int32_t n_views,
+                              int64_t total, Slab sl, uint32_t *__restrict__ counts, int32_t cshift)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= total) return;
@@ -433,38 +430,60 @@ __global__ void k_slab_counts(const uint32_t *__restrict__ skeys, const uint32_t
         const uint32_t vv = svals[i];
         // the count travels with the value unless it saturated
         const bool carried = cshift != 0 && (vv >> cshift) < count_sat(cshift);
-        if (done == nullptr && carried && sl.num_lo == 0 && sl.num_hi >= 1024) {
+        if (carried && sl.num_lo == 0 && sl.num_hi >= 1024) {
             c = vv >> cshift;  // one slab holds every element: no view lookup
         } else {
             const int v = find_view_of_elem(views, n_views, i);
             const ViewDev &C = views[v];
-            if (in_slab(C, i, sl)) {
-                const int64_t idx = (int64_t)C.elem_off + val_id(vv, cshift);
-                if (done == nullptr) {
-                    c = carried ? (vv >> cshift) : (uint32_t)ntiles[idx];
-                } else {
-                    short4 rc;
-                    SpanCode code;
-                    load_emit_record(codes, rect, idx, code, rc);
-                    Span32 sp = make_span32(0.f, 0.f, 1.f, 0.f, 1.f, true, 1.0f);
-                    if (!has_code(code)) {
-                        const float4 r0 = rec[2 * idx];
-                        const float4 r1 = rec[2 * idx + 1];
-                        sp = make_span32(r0.x, r0.y, r0.z, r0.w, r1.x, r1.w != 0.0f, support_limit(sigma_k));
-                    }
-                    for (int ty = rc.y; ty <= rc.w; ++ty) {
-                        int l, r;
-                        const bool any = has_code(code) ? code_span(code, ty - rc.y, rc.x, l, r)
-                                                        : row_span(sp, ty, rc.x, rc.z, tw, th, C.W, C.H, l, r);
-                        if (!any) continue;
-                        const uint8_t *d = done + C.tile_base + (uint32_t)ty * (uint32_t)C.tiles_x;
-                        for (int t = l; t <= r; ++t) c += d[t] ? 0u : 1u;
-                    }
-                }
-            }
+            if (in_slab(C, i, sl))
+                c = carried ? (vv >> cshift) : (uint32_t)ntiles[(int64_t)C.elem_off + val_id(vv, cshift)];
         }
     }
     counts[i] = c;
+}
+
+// Live tiles (not marked in `done`) of the rectangle [x0, x1] x [y0, y1] of a view, from its
+// summed-area table (k_live_table)
+__device__ __forceinline__ uint32_t live_tiles(const uint32_t *__restrict__ sat, int tiles_x, int x0, int y0, int x1,
+                                               int y1)
+{
+    const int64_t p = tiles_x + 1;
+    const uint32_t *a = sat + y0 * p, *b = sat + (y1 + 1) * p;
+    return (b[x1 + 1] - b[x0]) - (a[x1 + 1] - a[x0]);
+}
+
+// Summed-area table of one view's live tiles per block: sat[y][x] (y <= tiles_y, x <= tiles_x) =
+// live tiles in rows < y and columns < x. Waves take the rows' prefix sums in turn, then every
+// thread adds up columns.
+__global__ __launch_bounds__(kThreads) void k_live_table(const ViewDev *__restrict__ views,
+                                                         const uint8_t *__restrict__ done, uint32_t *__restrict__ table)
+{
+    const ViewDev &C = views[blockIdx.x];
+    const int tx = C.tiles_x, ty = C.tiles_y, lane = threadIdx.x & 63;
+    const int64_t p = tx + 1;
+    uint32_t *sat = table + C.sat_off;
+    const uint8_t *d = done + C.tile_base;
+    for (int x = threadIdx.x; x <= tx; x += kThreads) sat[x] = 0;
+    for (int y = threadIdx.x >> 6; y < ty; y += kWaves) {
+        uint32_t *row = sat + (y + 1) * p;
+        uint32_t before = 0;
+        if (lane == 0) row[0] = 0;
+        for (int x0 = 0; x0 < tx; x0 += 64) {
+            const bool live = x0 + lane < tx && !d[(int64_t)y * tx + x0 + lane];
+            const unsigned long long m = __ballot(live);
+            if (x0 + lane < tx) row[x0 + lane + 1] = before + (uint32_t)__popcll(m & (~0ull >> (63 - lane)));
+            before += (uint32_t)__popcll(m);
+        }
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x <= tx; x += kThreads) {
+        uint32_t sum = 0;
+#pragma unroll 8
+        for (int y = 1; y <= ty; ++y) {
+            sum += sat[y * p + x];
+            sat[y * p + x] = sum;
+        }
+    }
 }
 
 // Inclusive sum of x over the block's threads; *total receives the block sum.
@@ -496,13 +515,25 @@ __device__ __forceinline__ uint32_t block_scan_incl(uint32_t x, uint32_t *s_wsum
 // thread takes one row (a binary search in LDS finds its element), takes the
 // row's span (span code or the row_span rule, as in the count, without the
 // tiles already finished), and a block prefix sum of the rows' pair counts
-// gives each row its place in the output, where the thread writes its pairs.
+// gives each row its place in the output. The thread writes its row's pairs;
+// a row of kLongRow tiles or more is written by its whole wave, 64 tiles at a
+// time, so that one splat as wide as the image does not hold 63 lanes up.
+//
+// COUNT: instead writes counts[i], the pairs of every element of the slab `sl`
+// whose tiles are not marked in `done` (0 outside the slab). Each thread walking
+// its own element's rows and tiles took 14.0 ms of the 50 ms of a 3M-Gaussian solve
+// with needles and disks (12 views of 1297x840, two slabs, one lane); rows shared over
+// the block like the emission's, with the live tiles of a span from a summed-area table
+// and of a whole rectangle in one lookup, take 1.1 ms and the tables 0.15 ms.
+constexpr int kLongRow = 16;
+
+template <bool COUNT>
 __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t *__restrict__ skeys, const uint32_t *__restrict__ svals,
-                                                   const uint32_t *__restrict__ offsets, const uint32_t *__restrict__ counts,
+                                                   const uint32_t *__restrict__ offsets, uint32_t *__restrict__ counts,
                                                    const float4 *__restrict__ rec, const short4 *__restrict__ rect,
-                                                   const uint8_t *__restrict__ flags, const ViewDev *__restrict__ views,
-                                                   int32_t n_views, int64_t total, uint32_t capacity, int32_t tw, int32_t th,
-                                                   float sigma_k, const uint8_t *__restrict__ done,
+                                                   const ViewDev *__restrict__ views, int32_t n_views, int64_t total,
+                                                   uint32_t capacity, int32_t tw, int32_t th, float sigma_k, Slab sl,
+                                                   const uint8_t *__restrict__ done, const uint32_t *__restrict__ table,
                                                    uint32_t *__restrict__ tiles_out,
                                                    uint32_t *__restrict__ vals_out, unsigned long long *__restrict__ status,
                                                    int32_t gbits, const ulonglong2 *__restrict__ codes, int32_t cshift)
@@ -510,7 +541,8 @@ __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t *__restrict__ 
     __shared__ Span32 s_span[kThreads];
     __shared__ ulonglong2 s_code[kThreads];
     __shared__ short4 s_rc[kThreads];
-    __shared__ uint4 s_vw[kThreads];        // tile base, tiles per row, width, height of the element's view
+    __shared__ uint4 s_vw[kThreads];        // tile base, tiles per row, width | height << 16, view of the element
+    __shared__ uint32_t s_cnt[COUNT ? kThreads : 1];
     __shared__ uint32_t s_g[kThreads];
     __shared__ uint32_t s_roff[kThreads + 1];
     __shared__ uint32_t s_wsum[kWaves];
@@ -520,12 +552,15 @@ __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t *__restrict__ 
     const int64_t b0 = (int64_t)blockIdx.x * kThreads;
     const int64_t i = b0 + tid;
     const bool live = i < total && skeys[i] != 0xFFFFFFFFu;
-    const uint32_t cnt = live ? counts[i] : 0u;
-    if (tid == 0) s_lo = offsets[b0];
+    uint32_t cnt = 0;
+    if constexpr (!COUNT) {
+        cnt = live ? counts[i] : 0u;
+        if (tid == 0) s_lo = offsets[b0];
+    }
 
     uint32_t rows = 0;
-    if (cnt > 0) {
-        const int vw = find_view_of_elem(views, n_views, i);
+    const int vw = COUNT || cnt > 0 ? find_view_of_elem(views, n_views, i < total ? i : total - 1) : 0;
+    if (COUNT ? live && in_slab(views[vw], i, sl) : cnt > 0) {
         const uint32_t g = val_id(svals[i], cshift);
         const ViewDev &C = views[vw];
         const int64_t idx = (int64_t)C.elem_off + g;
@@ -542,17 +577,22 @@ __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t *__restrict__ 
         s_span[tid] = sp;
         s_code[tid] = make_ulonglong2(code.lo, code.hi);
         s_rc[tid] = rc;
-        s_vw[tid] = make_uint4(C.tile_base, (uint32_t)C.tiles_x, (uint32_t)C.W, (uint32_t)C.H);
+        s_vw[tid] = make_uint4(C.tile_base, (uint32_t)C.tiles_x, (uint32_t)C.W | ((uint32_t)C.H << 16), (uint32_t)vw);
         s_g[tid] = g;
         rows = (uint32_t)(rc.w - rc.y + 1);
+        if (COUNT && !has_code(code) && sp.full) {
+            cnt = live_tiles(table + C.sat_off, C.tiles_x, rc.x, rc.y, rc.z, rc.w);
+            rows = 0;
+        }
     }
+    if constexpr (COUNT) s_cnt[tid] = cnt;
     uint32_t n_rows = 0;
     const uint32_t incl = block_scan_incl(rows, s_wsum, &n_rows);
     s_roff[tid + 1] = incl;
     if (tid == 0) s_roff[0] = 0;
     for (uint32_t r = incl - rows; r < min(incl, kRowMap); ++r) s_rowelem[r] = (uint8_t)tid;
     __syncthreads();
-    const uint32_t lo = s_lo;
+    const uint32_t lo = COUNT ? 0u : s_lo;
 
     uint32_t dropped = 0, carry = 0;
     for (uint32_t c0 = 0; c0 < n_rows; c0 += kThreads) {
@@ -578,44 +618,69 @@ __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t *__restrict__ 
             const SpanCode code{cw.x, cw.y};
             const uint4 vw = s_vw[e];
             const bool any = has_code(code) ? code_span(code, row, rc.x, l, r)
-                                            : row_span(s_span[e], rc.y + row, rc.x, rc.z, tw, th, (int)vw.z, (int)vw.w, l, r);
+                                            : row_span(s_span[e], rc.y + row, rc.x, rc.z, tw, th, (int)(vw.z & 0xFFFFu), (int)(vw.z >> 16), l, r);
             if (any) {
-                if (done == nullptr) {
-                    n = (uint32_t)(r - l + 1);
-                } else {
-                    const uint8_t *d = done + vw.x + (uint32_t)(rc.y + row) * vw.y;
-                    for (int t = l; t <= r; ++t) n += d[t] ? 0u : 1u;
+                n = (uint32_t)(r - l + 1);
+                if (done != nullptr) {
+                    const int ty = rc.y + row;
+                    n = live_tiles(table + views[vw.w].sat_off, (int)vw.y, l, ty, r, ty);
                 }
-            } else {
-                r = l - 1;
+                if (COUNT && n > 0) atomicAdd(&s_cnt[e], n);
             }
         }
+        if constexpr (COUNT) continue;
         uint32_t round_total = 0;
         const uint32_t ex = block_scan_incl(n, s_wsum, &round_total) - n;
+        uint32_t p = lo + carry + ex;
+        uint32_t g = 0, rowbase = 0, outbase = 0;
         if (n > 0) {
-            const short4 rc = s_rc[e];
             const uint4 vw = s_vw[e];
-            const uint32_t g = s_g[e];
-            const uint32_t ty = (uint32_t)(rc.y + (int)(item - s_roff[e]));
-            const uint32_t rowbase = vw.x + ty * vw.y;
-            const uint32_t outbase = gbits ? rowbase - vw.x : rowbase;  // packed: the view's local tile
-            uint32_t p = lo + carry + ex;
+            g = s_g[e];
+            const uint32_t ty = (uint32_t)(s_rc[e].y + (int)(item - s_roff[e]));
+            rowbase = vw.x + ty * vw.y;
+            outbase = gbits ? rowbase - vw.x : rowbase;  // packed: the view's local tile
+        }
+        auto put = [&](uint32_t at, uint32_t tile, uint32_t id) {
+            if (at >= capacity) {
+                dropped++;
+            } else if (gbits) {
+                tiles_out[at] = (tile << gbits) | id;
+            } else {
+                tiles_out[at] = tile;
+                vals_out[at] = id;
+            }
+        };
+        const bool is_long = n > 0 && r - l + 1 >= kLongRow;
+        if (n > 0 && !is_long) {
             for (int t = l; t <= r; ++t) {
                 if (done != nullptr && done[rowbase + (uint32_t)t]) continue;
-                if (p < capacity) {
-                    if (gbits) {
-                        tiles_out[p] = ((outbase + (uint32_t)t) << gbits) | g;
-                    } else {
-                        tiles_out[p] = outbase + (uint32_t)t;
-                        vals_out[p] = g;
-                    }
-                } else {
-                    dropped++;
-                }
+                put(p, outbase + (uint32_t)t, g);
                 ++p;
             }
         }
+        const int lane = tid & 63;
+        unsigned long long longs = __ballot(is_long);
+        while (longs) {
+            const int j = __ffsll((long long)longs) - 1;
+            longs &= longs - 1ull;
+            const int lj = __builtin_amdgcn_readlane(l, j), rj = __builtin_amdgcn_readlane(r, j);
+            uint32_t pj = __builtin_amdgcn_readlane(p, j);
+            const uint32_t gj = __builtin_amdgcn_readlane(g, j), rbj = __builtin_amdgcn_readlane(rowbase, j);
+            const uint32_t obj = __builtin_amdgcn_readlane(outbase, j);
+            for (int t0 = lj; t0 <= rj; t0 += 64) {
+                const int t = t0 + lane;
+                const bool ok = t <= rj && !(done != nullptr && done[rbj + (uint32_t)t]);
+                const unsigned long long m = __ballot(ok);
+                if (ok) put(pj + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)), obj + (uint32_t)t, gj);
+                pj += (uint32_t)__popcll(m);
+            }
+        }
         carry += round_total;
+    }
+    if constexpr (COUNT) {
+        __syncthreads();
+        if (i < total) counts[i] = s_cnt[tid];
+        return;
     }
     if (tid == 0 && carry > 0) status_add(status, ST_PAIRS, (unsigned long long)carry);
     if (__ballot(dropped != 0) && dropped) {
@@ -869,17 +934,17 @@ hipError_t launch_gather_counts(hipStream_t s, const uint32_t *sorted_keys, cons
 
 hipError_t launch_emit(hipStream_t s, const uint32_t *sorted_keys, const uint32_t *sorted_vals,
                        const uint32_t *offsets, const uint32_t *counts, const float *rec, const int16_t *rect,
-                       const uint8_t *flags, const ViewDev *views, int32_t n_views, int64_t total,
-                       uint32_t capacity, int32_t tile_w, int32_t tile_h, float sigma_k, const uint8_t *done,
-                       uint32_t *tiles_out,
+                       const ViewDev *views, int32_t n_views, int64_t total, uint32_t capacity, int32_t tile_w,
+                       int32_t tile_h, float sigma_k, const uint8_t *done, const uint32_t *table, uint32_t *tiles_out,
                        uint32_t *vals_out, unsigned long long *status, int32_t gbits, const uint64_t *codes,
                        int32_t cshift)
 {
     if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_emit, dim3(grid_for(total, kThreads)), dim3(kThreads), 0, s, sorted_keys, sorted_vals, offsets,
-                       counts, reinterpret_cast<const float4 *>(rec), reinterpret_cast<const short4 *>(rect), flags,
-                       views, n_views, total, capacity, tile_w, tile_h, sigma_k, done, tiles_out, vals_out, status,
-                       gbits, reinterpret_cast<const ulonglong2 *>(codes), cshift);
+    hipLaunchKernelGGL(k_emit<false>, dim3(grid_for(total, kThreads)), dim3(kThreads), 0, s, sorted_keys, sorted_vals,
+                       offsets, const_cast<uint32_t *>(counts), reinterpret_cast<const float4 *>(rec),
+                       reinterpret_cast<const short4 *>(rect), views, n_views, total, capacity, tile_w, tile_h, sigma_k,
+                       Slab{0, 1024}, done, table, tiles_out, vals_out, status, gbits,
+                       reinterpret_cast<const ulonglong2 *>(codes), cshift);
     return hipGetLastError();
 }
 
@@ -902,20 +967,31 @@ hipError_t launch_slab_offsets(hipStream_t s, const uint32_t *offsets, const Vie
     return hipGetLastError();
 }
 
-hipError_t launch_slab_counts(hipStream_t s, const uint32_t *sorted_keys, const uint32_t *sorted_vals,
-                              const float *rec, const int16_t *rect, const uint8_t *flags, const int32_t *ntiles,
-                              const ViewDev *views, int32_t n_views, int64_t total, Slab slab, const uint8_t *done,
-                              int32_t tile_w, int32_t tile_h, float sigma_k, const uint64_t *codes,
-                              uint32_t *counts, int32_t cshift)
+hipError_t launch_live_table(hipStream_t s, const ViewDev *views, int32_t n_views, const uint8_t *done, uint32_t *table)
 {
-    if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_slab_counts, dim3(grid_for(total, 256)), dim3(256), 0, s, sorted_keys, sorted_vals,
-                       reinterpret_cast<const float4 *>(rec), reinterpret_cast<const short4 *>(rect), flags, ntiles,
-                       views, n_views, total, slab, done, tile_w, tile_h, sigma_k,
-                       reinterpret_cast<const ulonglong2 *>(codes), counts, cshift);
+    if (n_views <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_live_table, dim3((unsigned)n_views), dim3(kThreads), 0, s, views, done, table);
     return hipGetLastError();
 }
 
+hipError_t launch_slab_counts(hipStream_t s, const uint32_t *sorted_keys, const uint32_t *sorted_vals,
+                              const float *rec, const int16_t *rect, const int32_t *ntiles, const ViewDev *views,
+                              int32_t n_views, int64_t total, Slab slab, const uint8_t *done, const uint32_t *table,
+                              int32_t tile_w, int32_t tile_h, float sigma_k, const uint64_t *codes, uint32_t *counts,
+                              int32_t cshift)
+{
+    if (total == 0) return hipSuccess;
+    if (done == nullptr)
+        hipLaunchKernelGGL(k_slab_counts, dim3(grid_for(total, 256)), dim3(256), 0, s, sorted_keys, sorted_vals, ntiles,
+                           views, n_views, total, slab, counts, cshift);
+    else
+        hipLaunchKernelGGL(k_emit<true>, dim3(grid_for(total, kThreads)), dim3(kThreads), 0, s, sorted_keys, sorted_vals,
+                           (const uint32_t *)nullptr, counts, reinterpret_cast<const float4 *>(rec),
+                           reinterpret_cast<const short4 *>(rect), views, n_views, total, 0u, tile_w, tile_h, sigma_k,
+                           slab, done, table, (uint32_t *)nullptr, (uint32_t *)nullptr, (unsigned long long *)nullptr, 0,
+                           reinterpret_cast<const ulonglong2 *>(codes), cshift);
+    return hipGetLastError();
+}
 
 hipError_t launch_count_ranges(hipStream_t s, const uint32_t *counts, const uint32_t *starts, int64_t n_tiles,
                                uint32_t *ranges)
