@@ -284,6 +284,7 @@ struct Plan {
     uint64_t tiles = 0;
     uint64_t pixels = 0;
     uint64_t sat = 0;          // entries of the live-tile tables
+    uint64_t max_n = 0;        // most Gaussians of a view
 };
 
 // Device description of one view: camera, tile grid, and where its tiles,
@@ -333,6 +334,7 @@ void plan_add(Plan &pl, const fs_params *p, uint32_t scene, int64_t n, const fs_
         sg.alen = (uint32_t)n;
         sg.kbase = 0;
         pl.dsegs.push_back(sg);
+        pl.max_n = std::max<uint64_t>(pl.max_n, (uint64_t)n);
         pl.dblocks += (uint32_t)((n + kSortTile - 1) / kSortTile);
         pl.elems += (uint64_t)n;
         pl.tiles += (uint64_t)d.tiles_x * d.tiles_y;
@@ -396,7 +398,7 @@ int enqueue_lpt(fs_ctx *ctx, hipStream_t s, const uint32_t *ranges, uint64_t n_t
 {
     HIPCHECK(ctx, launch_tile_keys(s, ranges, (int64_t)n_tiles, k, items));
     const uint32_t blocks = (uint32_t)((n_tiles + kSortTile - 1) / kSortTile);
-    HIPCHECK(ctx, radix_sort(s, k, items, k2, v2, lseg, 1, blocks, 16, ws, nullptr, 1));
+    HIPCHECK(ctx, radix_sort(s, k, items, k2, v2, lseg, 1, blocks, 16, ws, nullptr, 1, n_tiles));
     return FS_OK;
 }
 
@@ -709,7 +711,7 @@ int fs_bin_sort(fs_ctx *ctx, const fs_proj *proj, const fs_camera *cams, const f
     // depth order of each view's emitting Gaussians (4 passes: result back in dk/dv)
     HIPCHECK(ctx, launch_depth_keys(s, proj->rec, proj->ntiles, proj->flags, views, V, total, dk, dv));
     HIPCHECK(ctx, radix_sort(s, dk, dv, (uint32_t *)ctx->dkeys2.p, (uint32_t *)ctx->dvals2.p,
-                             (const SegDev *)ctx->dsegs.p, V, pl.dblocks, 32, ctx->sort_ws.p, nullptr, 1));
+                             (const SegDev *)ctx->dsegs.p, V, pl.dblocks, 32, ctx->sort_ws.p, nullptr, 1, (uint64_t)n));
     HIPCHECK(ctx, launch_gather_counts(s, dk, dv, proj->ntiles, views, V, total, (uint32_t *)ctx->counts.p));
     HIPCHECK(ctx, scan_exclusive(s, (const uint32_t *)ctx->counts.p, (uint32_t *)ctx->offsets.p, total, ctx->npairs_dev,
                                  ctx->scan_ws.p));
@@ -746,7 +748,7 @@ int fs_bin_sort(fs_ctx *ctx, const fs_proj *proj, const fs_camera *cams, const f
                               nullptr, nullptr, k0, v0, ctx->status_dev));
     // without a host count, the device count caps the sort (entries past it are never read)
     HIPCHECK(ctx, radix_sort(s, k0, v0, k1, v1, (const SegDev *)ctx->psegs.p, 1, pblocks, passes * 8, ctx->sort_ws.p,
-                             n_pairs ? nullptr : ctx->npairs_dev, ptpb));
+                             n_pairs ? nullptr : ctx->npairs_dev, ptpb, (uint64_t)sort_len));
     HIPCHECK(ctx, launch_ranges(s, out->tiles, ctx->npairs_dev, (uint32_t)out->capacity, sort_len, out->ranges));
     return FS_OK;
 }
@@ -1121,6 +1123,7 @@ struct Chunk {
     uint32_t pair_cap = 0;    // slots used by this chunk
     uint32_t pblocks = 0;
     int32_t ptpb = 1;         // block tiles per block of the pair sort
+    uint64_t max_pairs_view = 0;  // largest segment of the packed pair sort
     std::vector<uint64_t> vpairs;  // planned pairs of each view
     // packed pair sort: one u32 item (tile in view << gbits | Gaussian) per pair,
     // one sort segment per view; used when both fit in 32 bits (single pass)
@@ -1220,7 +1223,7 @@ int enqueue_front(fs_batch *b, Work &w, Chunk &c, hipStream_t s)
                                  (float *)w.rec.p, (int16_t *)w.rect.p, (int32_t *)w.ntiles.p, (uint8_t *)w.flags.p,
                                  dk, dv, (uint64_t *)w.codes.p, ctx->status_dev));
     HIPCHECK(ctx, radix_sort(s, dk, dv, (uint32_t *)w.dkeys2.p, (uint32_t *)w.dvals2.p, (const SegDev *)c.dsegs.p,
-                             (int32_t)pl.views.size(), pl.dblocks, 32, w.sort_ws.p, nullptr, 1));
+                             (int32_t)pl.views.size(), pl.dblocks, 32, w.sort_ws.p, nullptr, 1, pl.max_n));
     return FS_OK;
 }
 
@@ -1294,7 +1297,7 @@ int enqueue_slabs(fs_batch *b, Work &w, Chunk &c, int chunk_idx, hipStream_t s, 
             HIPCHECK(ctx, launch_pair_segs(s, (const uint32_t *)w.offsets.p, (const ViewDev *)c.views.p, V, total, np,
                                            c.pair_cap, (SegDev *)c.psegs.p, ctx->status_dev));
             HIPCHECK(ctx, radix_sort_packed(s, pt, pta, pv, (const SegDev *)c.psegs.p, V, c.pblocks, c.gbits, c.tbits,
-                                            w.sort_ws.p, c.ptpb, tcount));
+                                            w.sort_ws.p, c.ptpb, c.max_pairs_view, tcount));
         } else {
             HIPCHECK(ctx, launch_emit(s, dk, dv, (const uint32_t *)w.offsets.p, (const uint32_t *)w.counts.p,
                                       (const float *)w.rec.p, (const int16_t *)w.rect.p,
@@ -1302,7 +1305,7 @@ int enqueue_slabs(fs_batch *b, Work &w, Chunk &c, int chunk_idx, hipStream_t s, 
                                       b->p.sigma_k, dn, table, k0, v0, ctx->status_dev, 0,
                                       (const uint64_t *)w.codes.p, c.cshift));
             HIPCHECK(ctx, radix_sort(s, k0, v0, k1, v1, (const SegDev *)c.psegs.p, 1, c.pblocks, c.passes * 8,
-                                     w.sort_ws.p, np, c.ptpb, tcount, false));
+                                     w.sort_ws.p, np, c.ptpb, c.pair_cap, tcount, false));
         }
         HIPCHECK(ctx, scan_exclusive(s, tcount, tstart, (int64_t)pl.tiles, nullptr, w.tscan_ws.p));
         HIPCHECK(ctx, launch_count_ranges(s, tcount, tstart, (int64_t)pl.tiles, (uint32_t *)w.ranges.p));
@@ -1620,6 +1623,7 @@ int batch_build(fs_batch *b, const fs_scene *scenes, int32_t n_scenes)
                 for (size_t j = 0; j < c.vpairs.size(); ++j) {
                     const uint64_t capj = std::min<uint64_t>(c.vpairs[j] + c.vpairs[j] / 64 + 256, c.pair_cap);
                     ps.push_back(SegDev{0, (uint32_t)capj, blk, 0, c.plan.views[j].tile_base});
+                    c.max_pairs_view = std::max(c.max_pairs_view, capj);
                     blk += (uint32_t)std::max<uint64_t>(1, (capj + span - 1) / span);
                 }
                 c.pblocks = blk;

@@ -159,11 +159,13 @@ hipError_t launch_depth_keys(hipStream_t s, const float *rec, const int32_t *nti
 // an even number of passes the result is in (keys, vals), after an odd number
 // in (keys_alt, vals_alt). key_count (optional, zeroed by the caller, one u32
 // per key value) receives the number of items of each key; with
-// last_keys = false the last pass writes the values only.
+// last_keys = false the last pass writes the values only. max_len: no segment is
+// longer (0: not known); short segments take fewer launches.
 size_t radix_ws_bytes(uint32_t n_blocks);
 hipError_t radix_sort(hipStream_t s, uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt,
                       const SegDev *segs, int32_t n_segs, uint32_t n_blocks, int32_t bits, void *ws,
-                      const uint32_t *len_dev, int32_t tpb, uint32_t *key_count = nullptr, bool last_keys = true);
+                      const uint32_t *len_dev, int32_t tpb, uint64_t max_len, uint32_t *key_count = nullptr,
+                      bool last_keys = true);
 // block tiles per block for a single-segment sort of n_items
 int32_t radix_tiles_per_block(uint64_t n_items);
 
@@ -175,7 +177,7 @@ int32_t radix_tiles_per_block(uint64_t n_items);
 // radix_sort.
 hipError_t radix_sort_packed(hipStream_t s, uint32_t *items, uint32_t *items_alt, uint32_t *ids_out,
                              const SegDev *segs, int32_t n_segs, uint32_t n_blocks, int32_t gbits, int32_t tbits,
-                             void *ws, int32_t tpb, uint32_t *key_count);
+                             void *ws, int32_t tpb, uint64_t max_len, uint32_t *key_count);
 
 // Per-view segments of the pairs emitted this run: segs[j].off/alen from the
 // device offsets (pairs beyond the planned capacity segs[j].len, or beyond

@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
                                                             int32_t shift, const uint32_t *__restrict__ offs,
                                                             const uint32_t *__restrict__ len_dev, int32_t tpb,
                                                             uint32_t *__restrict__ key_count, uint32_t dmask,
-                                                            int32_t kshift, uint32_t vmask)
+                                                            int32_t kshift, uint32_t vmask, int32_t raw)
 {
     __shared__ uint32_t s_cnt[kWaves][256];
     __shared__ uint32_t s_dstart[256];
@@ -288,9 +288,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 
     const SegInfo si = seg_of_block(segs, n_segs, blockIdx.x, len_dev, tpb);
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // s_gofs comes from one exclusive scan over the [segment][digit][block]
-    // counts of all segments, so it is already a position in the whole array
-    s_gofs[threadIdx.x] = offs[(int64_t)si.blk0 * 256 + (int64_t)threadIdx.x * si.bps + si.lb];
+    const uint32_t *row = offs + (int64_t)si.blk0 * 256 + (int64_t)threadIdx.x * si.bps;
+    if (raw) {
+        // offs holds the counts themselves: add up this digit's in the segment, and its in
+        // the blocks before this one
+        uint32_t all = 0, before = 0;
+#pragma unroll 8
+        for (uint32_t b = 0; b < si.bps; ++b) {
+            const uint32_t c = row[b];
+            all += c;
+            before += b < si.lb ? c : 0u;
+        }
+        uint32_t tot;
+        const uint32_t ex = block_excl_scan(all, s_wsum, tot);
+        s_gofs[threadIdx.x] = (uint32_t)(si.base - (int64_t)si.lb * kTile * tpb) + ex + before;
+    } else {
+        // offs comes from one exclusive scan over the [segment][digit][block]
+        // counts of all segments, so it is already a position in the whole array
+        s_gofs[threadIdx.x] = row[si.lb];
+    }
     const unsigned long long lt = (1ull << lane) - 1ull;
     const int dbits = 32 - __clz(dmask);  // digit width (dmask is 2^dbits - 1)
 
@@ -375,6 +391,98 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
         }
         __syncthreads();
         s_gofs[threadIdx.x] += tile_count;
+    }
+}
+
+// All passes of a sort whose segments fit one block tile each, in one launch: the block keeps its
+// segment's items in registers and reorders them through LDS, 8 bits at a time, with the ranking of
+// k_radix_scatter. The result goes to (kout, vout), which may be (kin, vin): every item is read
+// before any is written. Launches bound such sorts: the depth and tile sorts of a 2000-Gaussian
+// scene's 8 views took 18 launches and take 2; the whole solve went from 390 to 322 us.
+__global__ __launch_bounds__(kThreads) void k_sort_block(const uint32_t *kin, const uint32_t *vin, uint32_t *kout,
+                                                         uint32_t *vout, const SegDev *__restrict__ segs,
+                                                         int32_t n_segs, int32_t bits,
+                                                         const uint32_t *__restrict__ len_dev)
+{
+    __shared__ uint32_t s_cnt[kWaves][256];
+    __shared__ uint32_t s_dstart[256];
+    __shared__ uint32_t s_wsum[kWaves];
+    __shared__ uint32_t s_k[kTile], s_v[kTile];
+    const SegInfo si = seg_of_block(segs, n_segs, blockIdx.x, len_dev, 1);
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, n = si.nvalid;
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    const int rounds = (n + kThreads - 1) / kThreads;  // items per thread that are used
+    uint32_t key[kItems], val[kItems];
+    // wave w holds items [w * 64 * rounds, (w + 1) * 64 * rounds), 64 per round
+    const int first = w * 64 * rounds + lane;
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        const int i = first + r * 64;
+        const bool ok = r < rounds && i < n;
+        key[r] = ok ? kin[si.base + i] : 0xFFFFFFFFu;
+        val[r] = ok ? vin[si.base + i] : 0u;
+    }
+    for (int shift = 0; shift < bits; shift += 8) {
+        for (int i = threadIdx.x; i < kWaves * 256; i += kThreads) (&s_cnt[0][0])[i] = 0;
+        __syncthreads();
+        uint32_t rnk[kItems];
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            if (r >= rounds) break;
+            // items past the end rank behind every other of their digit: they come last
+            const uint32_t d = (key[r] >> shift) & 255u;
+            uint32_t plo = ~0u, phi = ~0u;
+#pragma unroll
+            for (int bit = 0; bit < 8; ++bit) {
+                const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)d, (unsigned)bit, 1u);
+                const unsigned long long bb = __ballot(m != 0u);
+                plo &= ~((uint32_t)bb ^ m);
+                phi &= ~((uint32_t)(bb >> 32) ^ m);
+            }
+            const unsigned long long peers = ((unsigned long long)phi << 32) | plo;
+            const uint32_t before = s_cnt[w][d];
+            rnk[r] = before + (uint32_t)__popcll(peers & lt);
+            __builtin_amdgcn_wave_barrier();
+            if ((peers & lt) == 0ull) s_cnt[w][d] = before + (uint32_t)__popcll(peers);
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        {
+            const int d = threadIdx.x;
+            uint32_t run = 0;
+#pragma unroll
+            for (int i = 0; i < kWaves; ++i) {
+                const uint32_t c = s_cnt[i][d];
+                s_cnt[i][d] = run;
+                run += c;
+            }
+            uint32_t tot;
+            s_dstart[d] = block_excl_scan(run, s_wsum, tot);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            if (r >= rounds) break;
+            const uint32_t d = (key[r] >> shift) & 255u;
+            const uint32_t pos = s_dstart[d] + s_cnt[w][d] + rnk[r];
+            s_k[pos] = key[r];
+            s_v[pos] = val[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            if (r >= rounds) break;
+            key[r] = s_k[first + r * 64];
+            val[r] = s_v[first + r * 64];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        const int i = first + r * 64;
+        if (r < rounds && i < n) {
+            if (kout) kout[si.base + i] = key[r];
+            vout[si.base + i] = val[r];
+        }
     }
 }
 
@@ -840,26 +948,45 @@ size_t radix_ws_bytes(uint32_t n_blocks)
     return (size_t)(2 * hist * 4 + scan_levels_bytes(hist) + 512);
 }
 
+// With few blocks, every block of a scatter adds up its segment's counts itself (at most 64 KB,
+// from L2): no launches for their scan. A solve of one 100k-Gaussian view after another goes from
+// 2449 to 2329 us, 16 small scenes in one batch from 866 to 811 us. Longer rows cost every block
+// more than the scan: up to 256 blocks a segment, a million Gaussians over 40 views took 17.7 ms
+// instead of 16.3.
+static bool raw_counts(uint32_t n_blocks, uint64_t max_blocks_per_seg)
+{
+    return n_blocks <= 1024 && max_blocks_per_seg > 0 && max_blocks_per_seg <= 64;
+}
+
 hipError_t radix_sort(hipStream_t s, uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt,
                       const SegDev *segs, int32_t n_segs, uint32_t n_blocks, int32_t bits, void *ws,
-                      const uint32_t *len_dev, int32_t tpb, uint32_t *key_count, bool last_keys)
+                      const uint32_t *len_dev, int32_t tpb, uint64_t max_len, uint32_t *key_count, bool last_keys)
 {
     if (n_blocks == 0 || n_segs == 0) return hipSuccess;
     if (tpb < 1) return hipErrorInvalidValue;
+    if (max_len <= (uint64_t)kTile && max_len > 0 && key_count == nullptr) {
+        const bool odd = ((bits + 7) / 8) % 2 == 1;
+        hipLaunchKernelGGL(k_sort_block, dim3(n_blocks), dim3(kThreads), 0, s, keys, vals,
+                           last_keys ? (odd ? keys_alt : keys) : nullptr, odd ? vals_alt : vals, segs, n_segs, bits,
+                           len_dev);
+        return hipGetLastError();
+    }
     const int64_t hist_n = (int64_t)n_blocks * 256;
     uint32_t *hist = (uint32_t *)ws;
     uint32_t *offs = hist + hist_n;
     void *scan_ws = offs + hist_n;
+    const bool raw = raw_counts(n_blocks, (max_len + (uint64_t)kTile * tpb - 1) / ((uint64_t)kTile * tpb));
     uint32_t *ki = keys, *vi = vals, *ko = keys_alt, *vo = vals_alt;
     for (int shift = 0; shift < bits; shift += 8) {
         hipLaunchKernelGGL(k_radix_hist, dim3(n_blocks), dim3(kThreads), 0, s, ki, segs, n_segs, shift, hist, len_dev,
                            tpb, 255u);
-        hipError_t e = scan_exclusive(s, hist, offs, hist_n, nullptr, scan_ws);
+        hipError_t e = raw ? hipGetLastError() : scan_exclusive(s, hist, offs, hist_n, nullptr, scan_ws);
         if (e != hipSuccess) return e;
         const bool last = shift + 8 >= bits;
         hipLaunchKernelGGL(k_radix_scatter<true>, dim3(n_blocks), dim3(kThreads), 0, s, ki, vi,
-                           (last && !last_keys) ? nullptr : ko, vo, segs, n_segs, shift, (const uint32_t *)offs,
-                           len_dev, tpb, last ? key_count : nullptr, 255u, 0, 0u);
+                           (last && !last_keys) ? nullptr : ko, vo, segs, n_segs, shift,
+                           (const uint32_t *)(raw ? hist : offs), len_dev, tpb, last ? key_count : nullptr, 255u, 0, 0u,
+                           raw ? 1 : 0);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         uint32_t *tk = ki, *tv = vi;
@@ -870,7 +997,7 @@ hipError_t radix_sort(hipStream_t s, uint32_t *keys, uint32_t *vals, uint32_t *k
 
 hipError_t radix_sort_packed(hipStream_t s, uint32_t *items, uint32_t *items_alt, uint32_t *ids_out,
                              const SegDev *segs, int32_t n_segs, uint32_t n_blocks, int32_t gbits, int32_t tbits,
-                             void *ws, int32_t tpb, uint32_t *key_count)
+                             void *ws, int32_t tpb, uint64_t max_len, uint32_t *key_count)
 {
     if (n_blocks == 0 || n_segs == 0) return hipSuccess;
     if (tpb < 1 || gbits < 1 || tbits < 1 || tbits > 16 || gbits + tbits > 32) return hipErrorInvalidValue;
@@ -883,6 +1010,7 @@ hipError_t radix_sort_packed(hipStream_t s, uint32_t *items, uint32_t *items_alt
     const int passes = tbits <= 8 ? 1 : 2;
     const int d0 = passes == 1 ? tbits : (tbits + 1) / 2;
     const uint32_t vmask = gbits == 32 ? 0xFFFFFFFFu : ((1u << gbits) - 1u);
+    const bool raw = raw_counts(n_blocks, (max_len + (uint64_t)kTile * tpb - 1) / ((uint64_t)kTile * tpb));
     const uint32_t *ki = items;
     for (int p = 0; p < passes; ++p) {
         const int shift = gbits + (p == 0 ? 0 : d0);
@@ -891,12 +1019,12 @@ hipError_t radix_sort_packed(hipStream_t s, uint32_t *items, uint32_t *items_alt
         const bool last = p + 1 == passes;
         hipLaunchKernelGGL(k_radix_hist, dim3(n_blocks), dim3(kThreads), 0, s, ki, segs, n_segs, shift, hist,
                            (const uint32_t *)nullptr, tpb, dmask);
-        hipError_t e = scan_exclusive(s, hist, offs, hist_n, nullptr, scan_ws);
+        hipError_t e = raw ? hipGetLastError() : scan_exclusive(s, hist, offs, hist_n, nullptr, scan_ws);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_radix_scatter<false>, dim3(n_blocks), dim3(kThreads), 0, s, ki, (const uint32_t *)nullptr,
                            last ? nullptr : items_alt, last ? ids_out : nullptr, segs, n_segs, shift,
-                           (const uint32_t *)offs, (const uint32_t *)nullptr, tpb, last ? key_count : nullptr, dmask,
-                           gbits, vmask);
+                           (const uint32_t *)(raw ? hist : offs), (const uint32_t *)nullptr, tpb,
+                           last ? key_count : nullptr, dmask, gbits, vmask, raw ? 1 : 0);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         ki = items_alt;
