@@ -343,12 +343,16 @@ void plan_add(Plan &pl, const fs_params *p, uint32_t scene, int64_t n, const fs_
         moff += (uint64_t)c.width * c.height;
     }
     const uint32_t bpv = (uint32_t)((n + 255) / 256);
-    for (int v = first; v < (int)pl.views.size(); v += kProjViews) {
+    const int last = (int)pl.views.size();
+    // as many views per Gaussian load as leave kProjBlocks blocks
+    const int per_task =
+        (int)std::min<uint64_t>(kProjViews, std::max<uint64_t>(1, (uint64_t)bpv * (last - first) / kProjBlocks));
+    for (int v = first; v < last; v += per_task) {
         ProjTask t;
         t.blk0 = pl.proj_blocks;
         t.scene = scene;
         t.v0 = (uint32_t)v;
-        t.nv = (uint32_t)std::min<int>(kProjViews, (int)pl.views.size() - v);
+        t.nv = (uint32_t)std::min(per_task, last - v);
         pl.tasks.push_back(t);
         pl.proj_blocks += bpv;
     }
