@@ -289,6 +289,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     const SegInfo si = seg_of_block(segs, n_segs, blockIdx.x, len_dev, tpb);
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const uint32_t *row = offs + (int64_t)si.blk0 * 256 + (int64_t)threadIdx.x * si.bps;
+    if (si.nvalid == 0) return;
+    uint32_t key[kItems];
+    // keys of block tile tb: wave w takes [w * 1024, (w + 1) * 1024) of it
+    auto load = [&](int tb) {
+        const int nvalid = min(kTile, si.nvalid - tb * kTile);
+        const int64_t base = si.base + (int64_t)tb * kTile;
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            const int li = w * (kItems * 64) + r * 64 + lane;
+            key[r] = li < nvalid ? kin[base + li] : 0xFFFFFFFFu;
+        }
+    };
+    load(0);
     if (raw) {
         // offs holds the counts themselves: add up this digit's in the segment, and its in
         // the blocks before this one
@@ -312,19 +325,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 
     for (int tb = 0; tb * kTile < si.nvalid; ++tb) {
         const int nvalid = min(kTile, si.nvalid - tb * kTile);
-        const uint32_t *kbase = kin + si.base + (int64_t)tb * kTile;
-        const uint32_t *vbase = VALS ? vin + si.base + (int64_t)tb * kTile : nullptr;
         for (int i = threadIdx.x; i < kWaves * 256; i += kThreads) (&s_cnt[0][0])[i] = 0;
         __syncthreads();
 
-        uint32_t key[kItems], val[VALS ? kItems : 1], rnk[kItems];
-#pragma unroll
-        for (int r = 0; r < kItems; ++r) {
-            const int li = w * (kItems * 64) + r * 64 + lane;
-            const bool ok = li < nvalid;
-            key[r] = ok ? kbase[li] : 0xFFFFFFFFu;
-            if constexpr (VALS) val[r] = ok ? vbase[li] : 0u;
-        }
+        uint32_t rnk[kItems];
 #pragma unroll
         for (int r = 0; r < kItems; ++r) {
             const uint32_t d = (key[r] >> shift) & dmask;
@@ -348,6 +352,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
+        // the values come after the ranking, which would spill with them
+        uint32_t val[VALS ? kItems : 1];
+        if constexpr (VALS) {
+            const int64_t base = si.base + (int64_t)tb * kTile;
+#pragma unroll
+            for (int r = 0; r < kItems; ++r) {
+                const int li = w * (kItems * 64) + r * 64 + lane;
+                val[r] = li < nvalid ? vin[base + li] : 0u;
+            }
+        }
         // per-digit totals, wave prefixes and the digit starts inside the block tile
         uint32_t tile_count;
         {
@@ -373,6 +387,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
             if constexpr (VALS) s_v[pos] = val[r];
         }
         __syncthreads();
+        // the next tile's keys are on their way while this one is written out
+        if ((tb + 1) * kTile < si.nvalid) load(tb + 1);
+#pragma unroll 4
         for (int i = threadIdx.x; i < nvalid; i += kThreads) {
             const uint32_t k = s_k[i];
             const uint32_t d = (k >> shift) & dmask;
