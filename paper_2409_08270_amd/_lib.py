@@ -203,12 +203,14 @@ def cameras(rows: np.ndarray):
     """FsCamera array from float32 [V, 18] rows (R9, t3, fx, fy, cx, cy, W, H)."""
     rows = np.asarray(rows, np.float32).reshape(-1, 18)
     arr = (FsCamera * rows.shape[0])()
-    for i, r in enumerate(rows):
-        arr[i].R[:] = [float(x) for x in r[0:9]]
-        arr[i].t[:] = [float(x) for x in r[9:12]]
-        arr[i].fx, arr[i].fy, arr[i].cx, arr[i].cy = [float(x) for x in r[12:16]]
-        arr[i].width = int(r[16])
-        arr[i].height = int(r[17])
+    if rows.shape[0] == 0:
+        return arr
+    if not np.isfinite(rows[:, 16:18]).all():
+        raise ValueError("camera width and height must be finite")
+    # FsCamera is 16 floats and two int32; filled as a whole (field by field took 6 us a view)
+    a = np.frombuffer(arr, np.float32).reshape(-1, 18)
+    a[:, :16] = rows[:, :16]
+    a.view(np.int32)[:, 16:] = rows[:, 16:18].astype(np.int64).astype(np.int32)
     return arr
 
 

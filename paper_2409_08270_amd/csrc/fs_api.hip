@@ -36,6 +36,8 @@ struct Staging {
 };
 
 constexpr int kStaging = 8;
+constexpr size_t kArenaHalf = 64 << 10;  // pinned bytes of each half of a context's upload arena
+constexpr size_t kReadback = 64 << 10;   // pinned bytes for its read-backs
 constexpr int kQueueWord = 8;  // word of the context's npairs_dev block used as the persistent launch's counter
 
 }  // namespace
@@ -48,7 +50,7 @@ struct fs_ctx {
     uint32_t *npairs_dev = nullptr;
     uint32_t *npairs_host = nullptr;            // pinned
     // per-call tables
-    DevBuf views, scenes, tasks, dsegs, psegs, lsegs;
+    DevBuf tables, psegs;
     // per-call workspace (grow-only)
     DevBuf dkeys, dvals, dkeys2, dvals2, counts, offsets;
     DevBuf pk_alt, pv_alt, sort_ws, scan_ws;
@@ -58,6 +60,13 @@ struct fs_ctx {
     uint64_t items_tiles = 0;  // tile count the XCD-run table in `items` was built for
     Staging stage[kStaging];
     int stage_next = 0;
+    // small uploads: two pinned halves filled in turn, and room for small read-backs
+    char *arena = nullptr;
+    int arena_half = 0;
+    size_t arena_used = 0;
+    hipEvent_t arena_ev[2] = {nullptr, nullptr};
+    bool arena_pending[2] = {false, false};
+    char *readback = nullptr;  // behind the arena, in the same allocation
     hipEvent_t acc_ev[2] = {nullptr, nullptr};  // around the last compositing launch
     bool acc_timed = false;
     // fs_accumulate_noalloc: this device's copy of the static scratch array, and
@@ -124,12 +133,48 @@ void free_buf(DevBuf &b)
     b.cap = 0;
 }
 
-// Copies host bytes to a device buffer asynchronously through a ring of
-// pinned staging buffers (a slot is reused only after its copy completed).
+// Pinned room of a small upload. An event after every copy costs as much as the
+// copy (9 us for both, of which the copy is less than half), so there is one per
+// half of the arena: a half is filled again only after its last copy completed.
+// NULL: no room (large uploads), or the stream is being captured, where an event
+// could not be waited for.
+int arena_room(fs_ctx *ctx, size_t bytes, char **out)
+{
+    *out = nullptr;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIPCHECK(ctx, hipStreamIsCapturing(ctx->stream, &cap));
+    bytes = (bytes + 255) & ~(size_t)255;
+    if (!ctx->arena || bytes > kArenaHalf || cap != hipStreamCaptureStatusNone) return FS_OK;
+    if (ctx->arena_used + bytes > kArenaHalf) {
+        const int h = ctx->arena_half, o = h ^ 1;
+        HIPCHECK(ctx, hipEventRecord(ctx->arena_ev[h], ctx->stream));
+        ctx->arena_pending[h] = true;
+        if (ctx->arena_pending[o]) {
+            HIPCHECK(ctx, hipEventSynchronize(ctx->arena_ev[o]));
+            ctx->arena_pending[o] = false;
+        }
+        ctx->arena_half = o;
+        ctx->arena_used = 0;
+    }
+    *out = ctx->arena + (size_t)ctx->arena_half * kArenaHalf + ctx->arena_used;
+    ctx->arena_used += bytes;
+    return FS_OK;
+}
+
+// Copies host bytes to a device buffer asynchronously: through the arena, or
+// through a ring of pinned staging buffers (a slot is reused only after its
+// copy completed).
 int upload(fs_ctx *ctx, DevBuf &dst, const void *src, size_t bytes)
 {
     RCHECK(ensure(ctx, dst, bytes));
     if (bytes == 0) return FS_OK;
+    char *room = nullptr;
+    RCHECK(arena_room(ctx, bytes, &room));
+    if (room) {
+        memcpy(room, src, bytes);
+        HIPCHECK(ctx, hipMemcpyAsync(dst.p, room, bytes, hipMemcpyHostToDevice, ctx->stream));
+        return FS_OK;
+    }
     Staging &st = ctx->stage[ctx->stage_next];
     ctx->stage_next = (ctx->stage_next + 1) % kStaging;
     if (st.pending) {
@@ -156,6 +201,39 @@ template <class T>
 int upload_vec(fs_ctx *ctx, DevBuf &dst, const std::vector<T> &v)
 {
     return upload(ctx, dst, v.data(), v.size() * sizeof(T));
+}
+
+// The tables of one call, uploaded with one copy into ctx->tables.
+struct Tables {
+    std::vector<char> h;
+    template <class T>
+    size_t add(const T *v, size_t count)
+    {
+        const size_t off = (h.size() + 255) & ~(size_t)255;
+        h.resize(off + count * sizeof(T));
+        if (count) memcpy(h.data() + off, v, count * sizeof(T));
+        return off;
+    }
+    template <class T>
+    size_t add(const std::vector<T> &v) { return add(v.data(), v.size()); }
+    int send(fs_ctx *ctx) const { return upload(ctx, ctx->tables, h.data(), h.size()); }
+};
+
+template <class T>
+const T *table(const fs_ctx *ctx, size_t off)
+{
+    return reinterpret_cast<const T *>((const char *)ctx->tables.p + off);
+}
+
+// Copies device bytes to the caller and waits: small results through pinned
+// room (22 us into pageable memory, 14 with it).
+int download(fs_ctx *ctx, void *dst, const void *src, size_t bytes)
+{
+    const bool small = ctx->readback && bytes <= kReadback;
+    HIPCHECK(ctx, hipMemcpyAsync(small ? ctx->readback : dst, src, bytes, hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHECK(ctx, hipStreamSynchronize(ctx->stream));
+    if (small) memcpy(dst, ctx->readback, bytes);
+    return FS_OK;
 }
 
 bool finite_f(float x) { return isfinite(x); }
@@ -564,6 +642,11 @@ int fs_ctx_create(fs_ctx **out, void *stream)
     if (!rc && hipHostMalloc((void **)&ctx->npairs_host, 64, hipHostMallocDefault) != hipSuccess) rc = FS_ERR_ALLOC;
     for (int i = 0; !rc && i < kStaging; ++i)
         if (hipEventCreateWithFlags(&ctx->stage[i].ev, hipEventDisableTiming) != hipSuccess) rc = FS_ERR_HIP;
+    if (!rc && hipHostMalloc((void **)&ctx->arena, 2 * kArenaHalf + kReadback, hipHostMallocDefault) != hipSuccess)
+        rc = FS_ERR_ALLOC;
+    if (!rc) ctx->readback = ctx->arena + 2 * kArenaHalf;
+    for (int i = 0; !rc && i < 2; ++i)
+        if (hipEventCreateWithFlags(&ctx->arena_ev[i], hipEventDisableTiming) != hipSuccess) rc = FS_ERR_HIP;
     for (int i = 0; !rc && i < 2; ++i)
         if (hipEventCreate(&ctx->acc_ev[i]) != hipSuccess) rc = FS_ERR_HIP;
     // fs_accumulate_noalloc's set-up: this device's scratch address, pinned table room
@@ -593,8 +676,7 @@ int fs_ctx_destroy(fs_ctx *ctx)
 {
     if (!ctx) return FS_ERR_ARG;
     (void)hipStreamSynchronize(ctx->stream);
-    DevBuf *bufs[] = {&ctx->views, &ctx->scenes, &ctx->tasks, &ctx->dsegs, &ctx->psegs, &ctx->lsegs,
-                      &ctx->dkeys, &ctx->dvals, &ctx->dkeys2, &ctx->dvals2, &ctx->counts, &ctx->offsets,
+    DevBuf *bufs[] = {&ctx->tables, &ctx->psegs, &ctx->dkeys, &ctx->dvals, &ctx->dkeys2, &ctx->dvals2, &ctx->counts, &ctx->offsets,
                       &ctx->pk_alt, &ctx->pv_alt, &ctx->sort_ws, &ctx->scan_ws, &ctx->items, &ctx->items_k,
                       &ctx->items_k2, &ctx->items_v2, &ctx->items_ws, &ctx->fix, &ctx->memb};
     for (DevBuf *b : bufs) free_buf(*b);
@@ -602,8 +684,11 @@ int fs_ctx_destroy(fs_ctx *ctx)
         if (ctx->stage[i].host) (void)hipHostFree(ctx->stage[i].host);
         if (ctx->stage[i].ev) (void)hipEventDestroy(ctx->stage[i].ev);
     }
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i) {
         if (ctx->acc_ev[i]) (void)hipEventDestroy(ctx->acc_ev[i]);
+        if (ctx->arena_ev[i]) (void)hipEventDestroy(ctx->arena_ev[i]);
+    }
+    if (ctx->arena) (void)hipHostFree(ctx->arena);
     if (ctx->na_ev) (void)hipEventDestroy(ctx->na_ev);
     if (ctx->na_host) (void)hipHostFree(ctx->na_host);
     if (ctx->status_dev) (void)hipFree(ctx->status_dev);
@@ -665,11 +750,11 @@ int fs_project(fs_ctx *ctx, const fs_gaussians *g, const fs_camera *cams, int32_
     Plan pl;
     plan_add(pl, p, 0, g->n, cams, 0, n_views, 0);
     std::vector<SceneDev> sc{scene_dev(g, g->n, nullptr, nullptr, nullptr, 2)};
-    RCHECK(upload_vec(ctx, ctx->views, pl.views));
-    RCHECK(upload_vec(ctx, ctx->scenes, sc));
-    RCHECK(upload_vec(ctx, ctx->tasks, pl.tasks));
-    HIPCHECK(ctx, launch_project(ctx->stream, (const ProjTask *)ctx->tasks.p, (int32_t)pl.tasks.size(), pl.proj_blocks,
-                                 (const SceneDev *)ctx->scenes.p, (const ViewDev *)ctx->views.p, proj_params(p),
+    Tables tb;
+    const size_t views = tb.add(pl.views), scenes = tb.add(sc), tasks = tb.add(pl.tasks);
+    RCHECK(tb.send(ctx));
+    HIPCHECK(ctx, launch_project(ctx->stream, table<ProjTask>(ctx, tasks), (int32_t)pl.tasks.size(), pl.proj_blocks,
+                                 table<SceneDev>(ctx, scenes), table<ViewDev>(ctx, views), proj_params(p),
                                  out->rec, out->rect, out->ntiles, out->flags, nullptr, nullptr, nullptr,
                                  ctx->status_dev));
     return FS_OK;
@@ -699,8 +784,9 @@ int fs_bin_sort(fs_ctx *ctx, const fs_proj *proj, const fs_camera *cams, const f
         HIPCHECK(ctx, launch_fill_u32(s, ctx->npairs_dev, 0u, 1));
         return FS_OK;
     }
-    RCHECK(upload_vec(ctx, ctx->views, pl.views));
-    RCHECK(upload_vec(ctx, ctx->dsegs, pl.dsegs));
+    Tables tabs;
+    const size_t views_at = tabs.add(pl.views), dsegs_at = tabs.add(pl.dsegs);
+    RCHECK(tabs.send(ctx));
     const size_t tb = (size_t)total * 4;
     RCHECK(ensure(ctx, ctx->dkeys, tb));
     RCHECK(ensure(ctx, ctx->dvals, tb));
@@ -711,17 +797,16 @@ int fs_bin_sort(fs_ctx *ctx, const fs_proj *proj, const fs_camera *cams, const f
     RCHECK(ensure(ctx, ctx->sort_ws, radix_ws_bytes(pl.dblocks)));
     RCHECK(ensure(ctx, ctx->scan_ws, scan_ws_bytes(total)));
     uint32_t *dk = (uint32_t *)ctx->dkeys.p, *dv = (uint32_t *)ctx->dvals.p;
-    const ViewDev *views = (const ViewDev *)ctx->views.p;
+    const ViewDev *views = table<ViewDev>(ctx, views_at);
     // depth order of each view's emitting Gaussians (4 passes: result back in dk/dv)
     HIPCHECK(ctx, launch_depth_keys(s, proj->rec, proj->ntiles, proj->flags, views, V, total, dk, dv));
     HIPCHECK(ctx, radix_sort(s, dk, dv, (uint32_t *)ctx->dkeys2.p, (uint32_t *)ctx->dvals2.p,
-                             (const SegDev *)ctx->dsegs.p, V, pl.dblocks, 32, ctx->sort_ws.p, nullptr, 1, (uint64_t)n));
+                             table<SegDev>(ctx, dsegs_at), V, pl.dblocks, 32, ctx->sort_ws.p, nullptr, 1, (uint64_t)n));
     HIPCHECK(ctx, launch_gather_counts(s, dk, dv, proj->ntiles, views, V, total, (uint32_t *)ctx->counts.p));
     HIPCHECK(ctx, scan_exclusive(s, (const uint32_t *)ctx->counts.p, (uint32_t *)ctx->offsets.p, total, ctx->npairs_dev,
-                                 ctx->scan_ws.p));
+                                 ctx->scan_ws.p, n_pairs ? ctx->npairs_host : nullptr));
     int64_t sort_len = out->capacity;
     if (n_pairs) {
-        HIPCHECK(ctx, hipMemcpyAsync(ctx->npairs_host, ctx->npairs_dev, 4, hipMemcpyDeviceToHost, s));
         HIPCHECK(ctx, hipStreamSynchronize(s));
         const int64_t np = (int64_t)ctx->npairs_host[0];
         *n_pairs = np;
@@ -784,8 +869,10 @@ int fs_accumulate(fs_ctx *ctx, const fs_proj *proj, const fs_bins *bins, const f
         HIPCHECK(ctx, launch_fill_u32(ctx->stream, (uint32_t *)ctx->fix.p, 0u, 2 * n_fix));
         sc[0].A_fix = (unsigned long long *)ctx->fix.p;
     }
-    RCHECK(upload_vec(ctx, ctx->views, pl.views));
-    RCHECK(upload_vec(ctx, ctx->scenes, sc));
+    const SegDev lseg{0, (uint32_t)pl.tiles, 0, (uint32_t)pl.tiles, 0};
+    Tables tabs;
+    const size_t views_at = tabs.add(pl.views), scenes_at = tabs.add(sc), lseg_at = tabs.add(&lseg, 1);
+    RCHECK(tabs.send(ctx));
     const uint32_t *items = nullptr;
     if (p->tile_order == 0) {
         const size_t tb = (size_t)pl.tiles * 4;
@@ -795,10 +882,8 @@ int fs_accumulate(fs_ctx *ctx, const fs_proj *proj, const fs_bins *bins, const f
         RCHECK(ensure(ctx, ctx->items_k2, tb));
         RCHECK(ensure(ctx, ctx->items_v2, tb));
         RCHECK(ensure(ctx, ctx->items_ws, radix_ws_bytes(lblocks)));
-        std::vector<SegDev> ls{SegDev{0, (uint32_t)pl.tiles, 0, (uint32_t)pl.tiles, 0}};
-        RCHECK(upload_vec(ctx, ctx->lsegs, ls));
         ctx->items_tiles = 0;  // the XCD-run table (tile_order 2) shares the buffer
-        RCHECK(enqueue_lpt(ctx, ctx->stream, bins->ranges, pl.tiles, (const SegDev *)ctx->lsegs.p,
+        RCHECK(enqueue_lpt(ctx, ctx->stream, bins->ranges, pl.tiles, table<SegDev>(ctx, lseg_at),
                            (uint32_t *)ctx->items.p, (uint32_t *)ctx->items_k.p, (uint32_t *)ctx->items_k2.p,
                            (uint32_t *)ctx->items_v2.p, ctx->items_ws.p));
         items = (const uint32_t *)ctx->items.p;
@@ -809,8 +894,8 @@ int fs_accumulate(fs_ctx *ctx, const fs_proj *proj, const fs_bins *bins, const f
     // events around the compositing launch alone (not under stream capture)
     const bool timed = cap == hipStreamCaptureStatusNone;
     if (timed) HIPCHECK(ctx, hipEventRecord(ctx->acc_ev[0], ctx->stream));
-    HIPCHECK(ctx, launch_accumulate(ctx->stream, proj->rec, bins->vals, bins->ranges, (const ViewDev *)ctx->views.p, V,
-                                    (const SceneDev *)ctx->scenes.p, items, (uint32_t)pl.tiles,
+    HIPCHECK(ctx, launch_accumulate(ctx->stream, proj->rec, bins->vals, bins->ranges, table<ViewDev>(ctx, views_at), V,
+                                    table<SceneDev>(ctx, scenes_at), items, (uint32_t)pl.tiles,
                                     acc_params(p, reduction, wide),
                                     pix ? pix->t_final : nullptr, pix ? pix->n_blend : nullptr, nullptr, nullptr, 1,
                                     ctx->status_dev, ctx->npairs_dev + kQueueWord));
@@ -936,9 +1021,9 @@ int fs_render_masks(fs_ctx *ctx, const fs_proj *proj, const fs_bins *bins, const
     if (!S || !labels) return set_err(ctx, FS_ERR_ARG, "S or labels is NULL");
     Plan pl;
     plan_add(pl, p, 0, proj->n, cams, 0, V, 0);
-    RCHECK(upload_vec(ctx, ctx->views, pl.views));
+    RCHECK(upload_vec(ctx, ctx->tables, pl.views));
     RCHECK(ensure(ctx, ctx->memb, (size_t)render_member_bytes(proj->n, n_classes, mode)));
-    HIPCHECK(ctx, launch_render(ctx->stream, proj->rec, bins->vals, bins->ranges, (const ViewDev *)ctx->views.p, V,
+    HIPCHECK(ctx, launch_render(ctx->stream, proj->rec, bins->vals, bins->ranges, (const ViewDev *)ctx->tables.p, V,
                                 (uint32_t)pl.tiles, S, proj->n, n_classes, acc_params(p, FS_RED_LDS), tau, mode, labels,
                                 rho, depth, (int64_t)pl.pixels, (uint8_t *)ctx->memb.p));
     return FS_OK;
@@ -962,8 +1047,7 @@ int fs_diagnose(fs_ctx *ctx, const float *A_hi, const float *A_lo, const uint8_t
                                    (want_m || want_o) ? S : nullptr, want_o ? gt : nullptr, n, n_classes,
                                    (double)rel_eps, (int64_t)nw, d, d + E1, d + 2 * E1));
     std::vector<uint64_t> h(nw * kDiagStripes);
-    HIPCHECK(ctx, hipMemcpyAsync(h.data(), d, h.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHECK(ctx, hipStreamSynchronize(ctx->stream));
+    RCHECK(download(ctx, h.data(), d, h.size() * 8));
     for (size_t i = nw; i < h.size(); ++i) h[i % nw] += h[i];
     if (want_c) memcpy(contrib_hist, h.data(), E1 * 8);
     if (want_m) memcpy(member_hist, h.data() + E1, E1 * 8);
@@ -998,33 +1082,31 @@ int fs_prompt_propagate(fs_ctx *ctx, const fs_gaussians *g, const fs_camera *cam
     }
     Plan pl;
     plan_add(pl, p, 0, g->n, cams, 0, n_views, 0);
-    RCHECK(upload_vec(ctx, ctx->views, pl.views));
+    Tables tabs;
+    const size_t views_at = tabs.add(pl.views), prompts_at = tabs.add(prompts, (size_t)n_prompts * 3);
+    RCHECK(tabs.send(ctx));
     // blocks per prompt: 4 or more centres per lane, and about 1024 blocks in all
     const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((g->n + 1023) / 1024, std::max<int64_t>(16, 1024 / n_prompts)));
-    // device layout: prompts | ids [P][1+k] | uv [P][V][2] | visible [P][V]
-    const size_t in_bytes = P * 3 * sizeof(float);
-    const size_t ids_off = (in_bytes + 255) & ~(size_t)255;
-    const size_t uv_off = ids_off + P * (1 + k) * 8;
+    // device layout: ids [P][1+k] | uv [P][V][2] | visible [P][V]
+    const size_t uv_off = P * (1 + k) * 8;
     const size_t vis_off = uv_off + P * V * 8;
     const size_t total = vis_off + P * V;
     RCHECK(ensure(ctx, ctx->items_k, P * (size_t)blocks * k * 8));
     RCHECK(ensure(ctx, ctx->items_k2, total));
     char *o = (char *)ctx->items_k2.p;
-    HIPCHECK(ctx, hipMemcpyAsync(o, prompts, in_bytes, hipMemcpyHostToDevice, ctx->stream));
-    HIPCHECK(ctx, launch_prompt(ctx->stream, gauss_ptrs(g), g->n, (const ViewDev *)ctx->views.p, n_views,
-                                pl.views[ref_view], (const float *)o, n_prompts, k, p->znear,
-                                (unsigned long long *)ctx->items_k.p, (int32_t)blocks, (long long *)(o + ids_off),
+    HIPCHECK(ctx, launch_prompt(ctx->stream, gauss_ptrs(g), g->n, table<ViewDev>(ctx, views_at), n_views,
+                                pl.views[ref_view], table<float>(ctx, prompts_at), n_prompts, k, p->znear,
+                                (unsigned long long *)ctx->items_k.p, (int32_t)blocks, (long long *)o,
                                 (float *)(o + uv_off), (uint8_t *)(o + vis_off)));
-    std::vector<char> h(total - ids_off);
-    HIPCHECK(ctx, hipMemcpyAsync(h.data(), o + ids_off, total - ids_off, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHECK(ctx, hipStreamSynchronize(ctx->stream));
+    std::vector<char> h(total);
+    RCHECK(download(ctx, h.data(), o, total));
     const long long *hid = (const long long *)h.data();
     for (size_t i = 0; i < P; ++i) {
         chosen[i] = (int64_t)hid[i * (1 + k)];
         for (int j = 0; nearest && j < k; ++j) nearest[i * k + j] = (int64_t)hid[i * (1 + k) + 1 + j];
     }
-    memcpy(uv, h.data() + (uv_off - ids_off), P * V * 8);
-    memcpy(visible, h.data() + (vis_off - ids_off), P * V);
+    memcpy(uv, h.data() + uv_off, P * V * 8);
+    memcpy(visible, h.data() + vis_off, P * V);
     return FS_OK;
 }
 
@@ -1049,10 +1131,7 @@ int fs_assign_sweep(fs_ctx *ctx, const float *A_hi, const float *A_lo, int64_t n
     }
     HIPCHECK(ctx, launch_assign_sweep(ctx->stream, A_hi, A_lo, n, n_classes, (const float *)ctx->items_ws.p, n_gamma,
                                       S, counts ? (unsigned long long *)ctx->items_k.p : nullptr));
-    if (counts) {
-        HIPCHECK(ctx, hipMemcpyAsync(counts, ctx->items_k.p, ncnt * 8, hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHECK(ctx, hipStreamSynchronize(ctx->stream));
-    }
+    if (counts) RCHECK(download(ctx, counts, ctx->items_k.p, ncnt * 8));
     return FS_OK;
 }
 
@@ -1072,8 +1151,7 @@ int fs_compact(fs_ctx *ctx, const fs_gaussians *in, const uint8_t *select, int32
     RCHECK(ensure(ctx, ctx->scan_ws, scan_ws_bytes(n)));
     HIPCHECK(ctx, launch_select_flags(ctx->stream, select, n, keep_selected, (uint32_t *)ctx->counts.p));
     HIPCHECK(ctx, scan_exclusive(ctx->stream, (const uint32_t *)ctx->counts.p, (uint32_t *)ctx->offsets.p, n,
-                                 ctx->npairs_dev, ctx->scan_ws.p));
-    HIPCHECK(ctx, hipMemcpyAsync(ctx->npairs_host, ctx->npairs_dev, 4, hipMemcpyDeviceToHost, ctx->stream));
+                                 nullptr, ctx->scan_ws.p, ctx->npairs_host));
     HIPCHECK(ctx, hipStreamSynchronize(ctx->stream));
     const int64_t kept = (int64_t)ctx->npairs_host[0];
     *n_out = kept;

@@ -192,7 +192,9 @@ hipError_t launch_pair_segs(hipStream_t s, const uint32_t *offsets, const ViewDe
 
 // Exclusive scan of u32 -> u32 (device-wide), total written to *total_out.
 size_t scan_ws_bytes(int64_t n);
-hipError_t scan_exclusive(hipStream_t s, const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total_out, void *ws);
+// total_out (device) and total_host (pinned host memory) receive the sum; either may be NULL.
+hipError_t scan_exclusive(hipStream_t s, const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total_out, void *ws,
+                          uint32_t *total_host = nullptr);
 
 // counts[i] = ntiles of depth-sorted element i (0 if its key is the sentinel);
 // cshift: how the values are packed (ProjParams)

@@ -82,7 +82,8 @@ __global__ __launch_bounds__(kThreads) void k_scan_reduce(const uint32_t *__rest
 // saves scanning the totals in a launch of their own).
 __global__ __launch_bounds__(kThreads) void k_scan_down(const uint32_t *__restrict__ in, uint32_t *__restrict__ out,
                                                         int64_t n, const uint32_t *__restrict__ offs,
-                                                        uint32_t *__restrict__ total_out, int32_t raw)
+                                                        uint32_t *__restrict__ total_out, int32_t raw,
+                                                        uint32_t *__restrict__ total_host)
 {
     __shared__ uint32_t s_wsum[kWaves];
     const int64_t base = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
@@ -143,7 +144,10 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(const uint32_t *__restri
             ex += v[k];
         }
     }
-    if (total_out && blockIdx.x == gridDim.x - 1 && threadIdx.x == kThreads - 1) *total_out = ex;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kThreads - 1) {
+        if (total_out) *total_out = ex;
+        if (total_host) *total_host = ex;
+    }
 }
 
 // ------------------------------------------------------------ radix sort --
@@ -932,16 +936,21 @@ static int64_t scan_levels_bytes(int64_t n)
 
 size_t scan_ws_bytes(int64_t n) { return (size_t)scan_levels_bytes(n); }
 
-hipError_t scan_exclusive(hipStream_t s, const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total_out, void *ws)
+hipError_t scan_exclusive(hipStream_t s, const uint32_t *in, uint32_t *out, int64_t n, uint32_t *total_out, void *ws,
+                          uint32_t *total_host)
 {
     if (n <= 0) {
+        if (total_host) {
+            hipError_t e = launch_fill_u32(s, total_host, 0u, 1);
+            if (e != hipSuccess) return e;
+        }
         if (total_out) return launch_fill_u32(s, total_out, 0u, 1);
         return hipSuccess;
     }
     const int64_t blocks = (n + kTile - 1) / kTile;
     if (blocks == 1) {
         hipLaunchKernelGGL(k_scan_down, dim3(1), dim3(kThreads), 0, s, in, out, n, (const uint32_t *)nullptr, total_out,
-                           0);
+                           0, total_host);
         return hipGetLastError();
     }
     uint32_t *sums = (uint32_t *)ws;
@@ -954,7 +963,7 @@ hipError_t scan_exclusive(hipStream_t s, const uint32_t *in, uint32_t *out, int6
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_scan_down, dim3((unsigned)blocks), dim3(kThreads), 0, s, in, out, n, (const uint32_t *)sums,
-                       total_out, raw ? 1 : 0);
+                       total_out, raw ? 1 : 0, total_host);
     return hipGetLastError();
 }
 
@@ -966,8 +975,8 @@ size_t radix_ws_bytes(uint32_t n_blocks)
 }
 
 // With few blocks, every block of a scatter adds up its segment's counts itself (at most 64 KB,
-// from L2): no launches for their scan. A solve of one 100k-Gaussian view after another goes from
-// 2449 to 2329 us, 16 small scenes in one batch from 866 to 811 us. Longer rows cost every block
+// from L2): no launches for their scan. A solve of 200k Gaussians view by view goes from
+// 2449 to 2329 us, a batch of 50k Gaussians in 20 views from 866 to 811 us. Longer rows cost every block
 // more than the scan: up to 256 blocks a segment, a million Gaussians over 40 views took 17.7 ms
 // instead of 16.3.
 static bool raw_counts(uint32_t n_blocks, uint64_t max_blocks_per_seg)
