@@ -301,7 +301,11 @@ __device__ __forceinline__ void accum_tile(const uint32_t tile, const float4 *__
         if (ts < 0.0f) active = false;  // this pixel's compositing ended in an earlier slab
         else T = ts;
     }
-    uint32_t nb_l = 0, ne_l = 0;      // this pixel's blends and in-support evaluations
+    uint32_t nb_l = 0;                // this pixel's blends
+    // the wave's blends and in-support evaluations, counted from the lane masks by the scalar unit:
+    // counters in every lane cost two vector instructions a step and spilled (8-scene batch with
+    // counters 21.8 -> 17.2 ms, 200k Gaussians view by view 2.10 -> 2.00 ms)
+    uint32_t nb_w = 0, ne_w = 0;
     uint32_t steps_w = 0;             // list entries this wave walked
     uint32_t staged = 0;              // list entries this block read (thread 0)
     bool live = active;
@@ -387,8 +391,10 @@ __device__ __forceinline__ void accum_tile(const uint32_t tile, const float4 *__
                 Tn = stop ? T : Tn;
             }
             if (COUNT) {
-                ne_l += (live && pw >= q2.w) ? 1u : 0u;
-                nb_l += (ok && !stop) ? 1u : 0u;
+                const bool blend = ok && !stop;
+                ne_w += (uint32_t)__popcll(__ballot(live && pw >= q2.w));
+                nb_w += (uint32_t)__popcll(__ballot(blend));
+                if (PIX) nb_l += blend ? 1u : 0u;
             }
             live = live && !stop;
             T = Tn;
@@ -543,13 +549,7 @@ __device__ __forceinline__ void accum_tile(const uint32_t tile, const float4 *__
         if (t_final) t_final[pix] = T;
         if (PIX && n_blend) n_blend[pix] = (int32_t)nb_l;
     }
-    // counters: summed over the wave, then the block in LDS, then one striped global atomic each
-    uint32_t nb_w = nb_l, ne_w = ne_l;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        nb_w += __shfl_xor(nb_w, off);
-        ne_w += __shfl_xor(ne_w, off);
-    }
+    // counters: the block's in LDS, then one striped global atomic each
     if (lane == 0) {
         atomicAdd(&s_misc[2], nb_w);
         atomicAdd(&s_misc[3], ne_w);
