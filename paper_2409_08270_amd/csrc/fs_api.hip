@@ -1146,11 +1146,15 @@ int fs_compact(fs_ctx *ctx, const fs_gaussians *in, const uint8_t *select, int32
     const int64_t n = in->n;
     *n_out = 0;
     if (n == 0) return FS_OK;
-    RCHECK(ensure(ctx, ctx->counts, (size_t)n * 4));
-    RCHECK(ensure(ctx, ctx->offsets, (size_t)n * 4));
-    RCHECK(ensure(ctx, ctx->scan_ws, scan_ws_bytes(n)));
-    HIPCHECK(ctx, launch_select_flags(ctx->stream, select, n, keep_selected, (uint32_t *)ctx->counts.p));
-    HIPCHECK(ctx, scan_exclusive(ctx->stream, (const uint32_t *)ctx->counts.p, (uint32_t *)ctx->offsets.p, n,
+    const int64_t tiles = (n + kCompactTile - 1) / kCompactTile;
+    RCHECK(ensure(ctx, ctx->counts, (size_t)tiles * 4));
+    RCHECK(ensure(ctx, ctx->offsets, (size_t)tiles * 4));
+    RCHECK(ensure(ctx, ctx->dkeys, (size_t)tiles * (kCompactTile / 8)));
+    RCHECK(ensure(ctx, ctx->scan_ws, scan_ws_bytes(tiles)));
+    unsigned long long *bits = (unsigned long long *)ctx->dkeys.p;
+    HIPCHECK(ctx, launch_select_sums(ctx->stream, select, n, keep_selected, (uint32_t *)ctx->counts.p,
+                                     bits));
+    HIPCHECK(ctx, scan_exclusive(ctx->stream, (const uint32_t *)ctx->counts.p, (uint32_t *)ctx->offsets.p, tiles,
                                  nullptr, ctx->scan_ws.p, ctx->npairs_host));
     HIPCHECK(ctx, hipStreamSynchronize(ctx->stream));
     const int64_t kept = (int64_t)ctx->npairs_host[0];
@@ -1167,8 +1171,7 @@ int fs_compact(fs_ctx *ctx, const fs_gaussians *in, const uint8_t *select, int32
                       const_cast<float *>(out->sz), const_cast<float *>(out->opacity)};
     for (int k = 0; k < 11; ++k)
         if (!dst[k]) return set_err(ctx, FS_ERR_ARG, "output Gaussian array %d is NULL", k);
-    HIPCHECK(ctx, launch_compact(ctx->stream, src, dst, (const uint32_t *)ctx->counts.p,
-                                 (const uint32_t *)ctx->offsets.p, n, index_map));
+    HIPCHECK(ctx, launch_compact(ctx->stream, src, dst, bits, n, (const uint32_t *)ctx->offsets.p, index_map));
     return FS_OK;
 }
 

@@ -333,9 +333,11 @@ hipError_t launch_prompt(hipStream_t s, const GaussPtrs &g, int64_t n, const Vie
 int sweep_max_gammas(int32_t E);
 hipError_t launch_assign_sweep(hipStream_t s, const float *A_hi, const float *A_lo, int64_t n, int32_t E,
                                const float *gammas_dev, int32_t n_gamma, uint8_t *S, unsigned long long *counts);
-hipError_t launch_select_flags(hipStream_t s, const uint8_t *select, int64_t n, int32_t keep_selected, uint32_t *flags);
-hipError_t launch_compact(hipStream_t s, const float *const in[11], float *const out[11], const uint32_t *flags,
-                          const uint32_t *pos, int64_t n, int64_t *index_map);
+constexpr int kCompactTile = 1024;  // Gaussians per block; bits: one per Gaussian, kCompactTile / 64 words per block
+hipError_t launch_select_sums(hipStream_t s, const uint8_t *select, int64_t n, int32_t keep_selected, uint32_t *sums,
+                              unsigned long long *bits);
+hipError_t launch_compact(hipStream_t s, const float *const in[11], float *const out[11],
+                          const unsigned long long *bits, int64_t n, const uint32_t *offs, int64_t *index_map);
 
 // ---- device helpers ------------------------------------------------------
 // View holding element i: the wave searches once (scalar) for its first
