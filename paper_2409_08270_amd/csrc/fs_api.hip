@@ -411,6 +411,7 @@ void plan_add(Plan &pl, const fs_params *p, uint32_t scene, int64_t n, const fs_
         sg.blk0 = pl.dblocks;
         sg.alen = (uint32_t)n;
         sg.kbase = 0;
+        sg.out = pl.elems;
         pl.dsegs.push_back(sg);
         pl.max_n = std::max<uint64_t>(pl.max_n, (uint64_t)n);
         pl.dblocks += (uint32_t)((n + kSortTile - 1) / kSortTile);

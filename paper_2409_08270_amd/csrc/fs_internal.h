@@ -62,16 +62,18 @@ struct ProjTask {
     uint32_t nv;
 };
 
-// radix-sort segment: elements [off, off + len), block tiles from blk0
-// A segment of a radix sort: items [off, off + min(len, alen)); `len` (the
-// planned capacity) fixes the segment's blocks, `alen` the items present.
-// kbase is added to the key's count index (packed pair sort).
+// A segment of a radix sort: items [off, off + min(len, alen)), blocks from
+// blk0; `len` (the planned capacity) fixes the segment's blocks, `alen` the
+// items present. Every pass writes the segment at `out`, the items of the
+// segments before it: the sorted array has no gaps, also where `alen` leaves
+// some out. kbase is added to the key's count index (packed pair sort).
 struct SegDev {
     uint64_t off;
     uint32_t len;
     uint32_t blk0;
     uint32_t alen;
     uint32_t kbase;
+    uint64_t out = 0;
 };
 
 struct ProjParams {
@@ -183,7 +185,7 @@ hipError_t radix_sort_packed(hipStream_t s, uint32_t *items, uint32_t *items_alt
                              const SegDev *segs, int32_t n_segs, uint32_t n_blocks, int32_t gbits, int32_t tbits,
                              void *ws, int32_t tpb, uint64_t max_len, uint32_t *key_count);
 
-// Per-view segments of the pairs emitted this run: segs[j].off/alen from the
+// Per-view segments of the pairs emitted this run: segs[j].off/alen/out from the
 // device offsets (pairs beyond the planned capacity segs[j].len, or beyond
 // `capacity`, are dropped and latched); len, blk0 and kbase stay as planned.
 hipError_t launch_pair_segs(hipStream_t s, const uint32_t *offsets, const ViewDev *views, int32_t n_views,

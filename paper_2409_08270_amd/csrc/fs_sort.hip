@@ -161,6 +161,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(const uint32_t *__restri
 // (segments' blk0 count super-tiles).
 struct SegInfo {
     int64_t base;     // first element of this super-tile
+    uint32_t out;     // first element of the segment's output
     int nvalid;       // valid items in the super-tile
     uint32_t bps;     // super-tiles of the segment
     uint32_t lb;      // super-tile index inside the segment
@@ -168,8 +169,9 @@ struct SegInfo {
     uint32_t kbase;   // added to count indexes
 };
 
+// `later`: the input is an earlier pass's output
 __device__ __forceinline__ SegInfo seg_of_block(const SegDev *__restrict__ segs, int32_t n_segs, uint32_t b,
-                                                const uint32_t *__restrict__ len_dev, int32_t tpb)
+                                                const uint32_t *__restrict__ len_dev, int32_t tpb, int32_t later)
 {
     int lo = 0, hi = n_segs - 1;
     while (lo < hi) {
@@ -187,7 +189,8 @@ __device__ __forceinline__ SegInfo seg_of_block(const SegDev *__restrict__ segs,
     r.kbase = sg.kbase;
     const int64_t rem = (int64_t)len - (int64_t)r.lb * span;
     r.nvalid = rem <= 0 ? 0 : (rem < span ? (int)rem : (int)span);
-    r.base = (int64_t)sg.off + (int64_t)r.lb * span;
+    r.out = (uint32_t)sg.out;
+    r.base = (int64_t)(later ? sg.out : sg.off) + (int64_t)r.lb * span;
     return r;
 }
 
@@ -202,10 +205,10 @@ __global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t *__restr
                                                          const SegDev *__restrict__ segs, int32_t n_segs,
                                                          int32_t shift, uint32_t *__restrict__ hist,
                                                          const uint32_t *__restrict__ len_dev, int32_t tpb,
-                                                         uint32_t dmask)
+                                                         uint32_t dmask, int32_t later)
 {
     __shared__ uint32_t s_h[kWaves][256];
-    const SegInfo si = seg_of_block(segs, n_segs, blockIdx.x, len_dev, tpb);
+    const SegInfo si = seg_of_block(segs, n_segs, blockIdx.x, len_dev, tpb, later);
     const int w = threadIdx.x >> 6;
     for (int i = threadIdx.x; i < kWaves * 256; i += kThreads) (&s_h[0][0])[i] = 0;
     __syncthreads();
@@ -281,7 +284,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
                                                             int32_t shift, const uint32_t *__restrict__ offs,
                                                             const uint32_t *__restrict__ len_dev, int32_t tpb,
                                                             uint32_t *__restrict__ key_count, uint32_t dmask,
-                                                            int32_t kshift, uint32_t vmask, int32_t raw)
+                                                            int32_t kshift, uint32_t vmask, int32_t raw, int32_t later)
 {
     __shared__ uint32_t s_cnt[kWaves][256];
     __shared__ uint32_t s_dstart[256];
@@ -290,7 +293,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     __shared__ uint32_t s_k[kTile];
     __shared__ uint32_t s_v[VALS ? kTile : 1];
 
-    const SegInfo si = seg_of_block(segs, n_segs, blockIdx.x, len_dev, tpb);
+    const SegInfo si = seg_of_block(segs, n_segs, blockIdx.x, len_dev, tpb, later);
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const uint32_t *row = offs + (int64_t)si.blk0 * 256 + (int64_t)threadIdx.x * si.bps;
     if (si.nvalid == 0) return;
@@ -318,10 +321,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
         }
         uint32_t tot;
         const uint32_t ex = block_excl_scan(all, s_wsum, tot);
-        s_gofs[threadIdx.x] = (uint32_t)(si.base - (int64_t)si.lb * kTile * tpb) + ex + before;
+        s_gofs[threadIdx.x] = si.out + ex + before;
     } else {
         // offs comes from one exclusive scan over the [segment][digit][block]
-        // counts of all segments, so it is already a position in the whole array
+        // counts of all segments, so it is already a position in the whole array (the
+        // segments' `out` are the same sums)
         s_gofs[threadIdx.x] = row[si.lb];
     }
     const unsigned long long lt = (1ull << lane) - 1ull;
@@ -429,7 +433,7 @@ __global__ __launch_bounds__(kThreads) void k_sort_block(const uint32_t *kin, co
     __shared__ uint32_t s_dstart[256];
     __shared__ uint32_t s_wsum[kWaves];
     __shared__ uint32_t s_k[kTile], s_v[kTile];
-    const SegInfo si = seg_of_block(segs, n_segs, blockIdx.x, len_dev, 1);
+    const SegInfo si = seg_of_block(segs, n_segs, blockIdx.x, len_dev, 1, 0);
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, n = si.nvalid;
     const unsigned long long lt = (1ull << lane) - 1ull;
     const int rounds = (n + kThreads - 1) / kThreads;  // items per thread that are used
@@ -887,27 +891,42 @@ __global__ void k_slab_offsets(const uint32_t *__restrict__ offsets, const ViewD
     out[i] = e < total_elems ? offsets[e] : *total_pairs;
 }
 
-// Segments of the packed pair sort, one per view (see launch_pair_segs).
-__global__ void k_pair_segs(const uint32_t *__restrict__ offsets, const ViewDev *__restrict__ views, int32_t n_views,
-                            int64_t total_elems, const uint32_t *__restrict__ total_pairs, uint32_t capacity,
-                            SegDev *__restrict__ segs, unsigned long long *__restrict__ status)
+// Segments of the packed pair sort, one per view (see launch_pair_segs). One
+// block: the lists of a view begin where the kept pairs of the views before it
+// end, as the tiles' ranges (a scan of the kept pairs' counts) do.
+__global__ __launch_bounds__(kThreads) void k_pair_segs(const uint32_t *__restrict__ offsets,
+                                                        const ViewDev *__restrict__ views, int32_t n_views,
+                                                        int64_t total_elems, const uint32_t *__restrict__ total_pairs,
+                                                        uint32_t capacity, SegDev *__restrict__ segs,
+                                                        unsigned long long *__restrict__ status)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n_views) return;
+    __shared__ uint32_t s_wsum[kWaves];
     const uint32_t np = min(*total_pairs, capacity);
-    const int64_t e0 = (int64_t)views[j].elem_off;
-    const int64_t e1 = j + 1 < n_views ? (int64_t)views[j + 1].elem_off : total_elems;
-    const uint32_t a = min(e0 < total_elems ? offsets[e0] : *total_pairs, np);
-    const uint32_t b = min(e1 < total_elems ? offsets[e1] : *total_pairs, np);
-    const uint32_t have = b > a ? b - a : 0u;
-    SegDev sg = segs[j];
-    sg.off = a;
-    sg.alen = min(have, sg.len);
-    if (have > sg.len) {
-        status_add(status, ST_DROPPED, (unsigned long long)(have - sg.len));
-        status_flag(status, (unsigned long long)FS_DEV_PAIR_OVERFLOW);
+    uint32_t before = 0;  // kept pairs of the views before j0
+    for (int j0 = 0; j0 < n_views; j0 += kThreads) {
+        const int j = j0 + (int)threadIdx.x;
+        uint32_t kept = 0, a = 0;
+        if (j < n_views) {
+            const int64_t e0 = (int64_t)views[j].elem_off;
+            const int64_t e1 = j + 1 < n_views ? (int64_t)views[j + 1].elem_off : total_elems;
+            a = min(e0 < total_elems ? offsets[e0] : *total_pairs, np);
+            const uint32_t b = min(e1 < total_elems ? offsets[e1] : *total_pairs, np);
+            const uint32_t have = b > a ? b - a : 0u;
+            kept = min(have, segs[j].len);
+            if (have > kept) {
+                status_add(status, ST_DROPPED, (unsigned long long)(have - kept));
+                status_flag(status, (unsigned long long)FS_DEV_PAIR_OVERFLOW);
+            }
+        }
+        uint32_t total;
+        const uint32_t ex = block_excl_scan(kept, s_wsum, total);
+        if (j < n_views) {
+            segs[j].off = a;
+            segs[j].alen = kept;
+            segs[j].out = before + ex;
+        }
+        before += total;
     }
-    segs[j] = sg;
 }
 
 inline unsigned grid_for(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
@@ -1005,14 +1024,14 @@ hipError_t radix_sort(hipStream_t s, uint32_t *keys, uint32_t *vals, uint32_t *k
     uint32_t *ki = keys, *vi = vals, *ko = keys_alt, *vo = vals_alt;
     for (int shift = 0; shift < bits; shift += 8) {
         hipLaunchKernelGGL(k_radix_hist, dim3(n_blocks), dim3(kThreads), 0, s, ki, segs, n_segs, shift, hist, len_dev,
-                           tpb, 255u);
+                           tpb, 255u, shift > 0 ? 1 : 0);
         hipError_t e = raw ? hipGetLastError() : scan_exclusive(s, hist, offs, hist_n, nullptr, scan_ws);
         if (e != hipSuccess) return e;
         const bool last = shift + 8 >= bits;
         hipLaunchKernelGGL(k_radix_scatter<true>, dim3(n_blocks), dim3(kThreads), 0, s, ki, vi,
                            (last && !last_keys) ? nullptr : ko, vo, segs, n_segs, shift,
                            (const uint32_t *)(raw ? hist : offs), len_dev, tpb, last ? key_count : nullptr, 255u, 0, 0u,
-                           raw ? 1 : 0);
+                           raw ? 1 : 0, shift > 0 ? 1 : 0);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         uint32_t *tk = ki, *tv = vi;
@@ -1044,13 +1063,13 @@ hipError_t radix_sort_packed(hipStream_t s, uint32_t *items, uint32_t *items_alt
         const uint32_t dmask = (1u << bits) - 1u;
         const bool last = p + 1 == passes;
         hipLaunchKernelGGL(k_radix_hist, dim3(n_blocks), dim3(kThreads), 0, s, ki, segs, n_segs, shift, hist,
-                           (const uint32_t *)nullptr, tpb, dmask);
+                           (const uint32_t *)nullptr, tpb, dmask, p);
         hipError_t e = raw ? hipGetLastError() : scan_exclusive(s, hist, offs, hist_n, nullptr, scan_ws);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_radix_scatter<false>, dim3(n_blocks), dim3(kThreads), 0, s, ki, (const uint32_t *)nullptr,
                            last ? nullptr : items_alt, last ? ids_out : nullptr, segs, n_segs, shift,
                            (const uint32_t *)(raw ? hist : offs), (const uint32_t *)nullptr, tpb,
-                           last ? key_count : nullptr, dmask, gbits, vmask, raw ? 1 : 0);
+                           last ? key_count : nullptr, dmask, gbits, vmask, raw ? 1 : 0, p);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         ki = items_alt;
@@ -1107,8 +1126,8 @@ hipError_t launch_pair_segs(hipStream_t s, const uint32_t *offsets, const ViewDe
                             unsigned long long *status)
 {
     if (n_views <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pair_segs, dim3(grid_for(n_views, 256)), dim3(256), 0, s, offsets, views, n_views,
-                       total_elems, total_pairs, capacity, segs, status);
+    hipLaunchKernelGGL(k_pair_segs, dim3(1), dim3(kThreads), 0, s, offsets, views, n_views, total_elems, total_pairs,
+                       capacity, segs, status);
     return hipGetLastError();
 }
 
