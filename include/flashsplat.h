@@ -409,6 +409,8 @@ int fs_prompt_propagate(fs_ctx *ctx, const fs_gaussians *g, const fs_camera *cam
  * FS_DEV_PAIR_OVERFLOW is latched; create a new batch then. */
 typedef struct fs_batch fs_batch;
 
+/* Descriptors may name the same A_hi and A_lo (one scene's views or masks split
+ * over several): their sums add up, and every assignment sees all of them. */
 typedef struct {
     fs_gaussians gauss;        /* device */
     const fs_camera *cams;     /* host [n_views] (copied at creation) */

@@ -548,6 +548,23 @@ __global__ void k_xcd_items(uint32_t *items, uint32_t n_tiles)
 // way; one of 1M x 17 from 40 views (0.6 times) 17.4 against 20.3 ms.
 bool wide_pays(int64_t words, uint64_t pixels) { return (uint64_t)words <= 8 * pixels; }
 
+// Do the sums of two of the scenes (or A_hi and A_lo of one) share memory, as those of one scene
+// split over two descriptors do? Float64 totals belong to one descriptor and replace what A held;
+// the two-sum adds, whatever the descriptors share.
+bool sums_overlap(const fs_scene *scenes, int32_t n_scenes)
+{
+    std::vector<std::pair<uintptr_t, uintptr_t>> r;
+    for (int i = 0; i < n_scenes; ++i) {
+        const uintptr_t bytes = (uintptr_t)scenes[i].gauss.n * (uintptr_t)scenes[i].n_classes * sizeof(float);
+        for (const float *a : {scenes[i].A_hi, scenes[i].A_lo})
+            if (a && bytes > 0) r.emplace_back((uintptr_t)a, (uintptr_t)a + bytes);
+    }
+    std::sort(r.begin(), r.end());
+    for (size_t i = 1; i < r.size(); ++i)
+        if (r[i].first < r[i - 1].second) return true;
+    return false;
+}
+
 // FS_RED_DET: pixels per call (per scene in a batch); see to_fix's range
 constexpr uint64_t kFixMaxPixels = (uint64_t)1 << 29;
 
@@ -1503,7 +1520,8 @@ int batch_build(fs_batch *b, const fs_scene *scenes, int32_t n_scenes)
         words += (int64_t)s.g.n * s.E;
         for (const fs_camera &c : s.cams) pixels += (uint64_t)c.width * (uint64_t)c.height;
     }
-    b->wide = b->o.reduction == FS_RED_LDS2SUM && words > 0 && wide_pays(words, pixels);
+    b->wide = b->o.reduction == FS_RED_LDS2SUM && words > 0 && wide_pays(words, pixels) &&
+              !sums_overlap(scenes, n_scenes);
     // without room for the float64 totals the two-sum into A_hi and A_lo does as well
     if (b->wide && batch_alloc(b, b->fix, (size_t)words * 8) != FS_OK) {
         (void)hipGetLastError();
