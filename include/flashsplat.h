@@ -240,12 +240,14 @@ int fs_bin_sort(fs_ctx *ctx, const fs_proj *proj, const fs_camera *cams, const f
  * processed over any number of calls). A_lo: same shape, or NULL; with
  * FS_RED_LDS2SUM the accumulated result is A_hi + A_lo. Where n * n_classes is
  * at most 8 times the call's pixels, the call sums in float64 totals (context
- * workspace of n * n_classes * 8 bytes) and A_hi, A_lo receive the float
- * nearest to each sum and the float nearest to the rest. Otherwise (and under
- * stream capture, or without room for the totals) A_lo receives the exact
- * rounding error of every addition into A_hi, and the partial sums of labels
- * that no 8x8 pixel block of a tile holds in 4 or more pixels (stray,
- * noise-like labels), which are small.
+ * workspace of n * n_classes * 8 bytes) and adds each total once: the float
+ * nearest to it into A_hi, the exact rounding error of that addition and the
+ * float nearest to the rest into A_lo. Otherwise (and under stream capture, or
+ * without room for the totals) A_lo receives the exact rounding error of every
+ * addition into A_hi, and the partial sums of labels that no 8x8 pixel block of
+ * a tile holds in 4 or more pixels (stray, noise-like labels), which are small.
+ * All additions are atomic: calls that overlap in time (other contexts or
+ * streams) may add into one A, except with FS_RED_DET.
  * FS_RED_DET: the call's weights are summed exactly as 64-bit fixed-point
  * integers in units of 2^-34 (each wave's float sum per (Gaussian, label) is
  * rounded once to that grid, about 3e-11), in a context workspace of

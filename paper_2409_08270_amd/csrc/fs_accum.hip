@@ -136,17 +136,23 @@ __device__ __forceinline__ T atomic_add(T *p, int64_t idx, T x)
     return __hip_atomic_fetch_add((G *)(p + idx), x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// adds x to hi[idx]; returns the rounding error, the exact two-sum of the value the
+// atomic found and x
+__device__ __forceinline__ float two_sum_add(float *hi, int64_t idx, float x)
+{
+    const float old = atomic_add(hi, idx, x);
+    const float s = old + x;
+    const float bp = s - old;
+    return (old - (s - bp)) + (x - bp);
+}
+
 __device__ __forceinline__ void add_global(float *hi, float *lo, int64_t idx, float x)
 {
     if (lo == nullptr) {
         (void)atomic_add(hi, idx, x);
         return;
     }
-    // exact two-sum of the value the atomic found and x
-    const float old = atomic_add(hi, idx, x);
-    const float s = old + x;
-    const float bp = s - old;
-    const float err = (old - (s - bp)) + (x - bp);
+    const float err = two_sum_add(hi, idx, x);
     if (err != 0.0f) (void)atomic_add(lo, idx, err);
 }
 
@@ -631,19 +637,27 @@ __global__ __launch_bounds__(256) void k_fix_finish(const unsigned long long *__
 }
 static_assert(kFixShift == 34, "k_fix_finish scales by 2^-34");
 
-// float64 totals into A_hi + A_lo, one thread per entry: hi is the float nearest
-// to the value, lo the float nearest to what remains
+// float64 totals into A_hi + A_lo, one thread per entry, as the float nearest to the total and the
+// float nearest to what remains. ADD: added to what A holds with atomics (an exact two-sum into A_hi,
+// its error and the rest into A_lo), so that calls that overlap in time may add into one A; else in
+// its place.
+template <bool ADD>
 __global__ __launch_bounds__(256) void k_wide_finish(const double *__restrict__ wide, float *__restrict__ A_hi,
-                                                     float *__restrict__ A_lo, int64_t count, int32_t add)
+                                                     float *__restrict__ A_lo, int64_t count)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= count) return;
     const double v = wide[i];
-    if (add && v == 0.0) return;
+    if (ADD && v == 0.0) return;
     float hi, lo;
-    wide_split(add ? ((double)A_hi[i] + (double)A_lo[i]) + v : v, hi, lo);
-    A_hi[i] = hi;
-    A_lo[i] = lo;
+    wide_split(v, hi, lo);
+    if constexpr (ADD) {
+        const float rest = two_sum_add(A_hi, i, hi) + lo;
+        if (rest != 0.0f) (void)atomic_add(A_lo, i, rest);
+    } else {
+        A_hi[i] = hi;
+        A_lo[i] = lo;
+    }
 }
 
 // resident workgroups of a compositing kernel on this device (cached per kernel)
@@ -698,8 +712,9 @@ hipError_t launch_fix_finish(hipStream_t s, const unsigned long long *fix, float
 hipError_t launch_wide_finish(hipStream_t s, const double *wide, float *A_hi, float *A_lo, int64_t count, int32_t add)
 {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_wide_finish, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, wide, A_hi, A_lo, count,
-                       add);
+    const dim3 grid((unsigned)((count + 255) / 256));
+    if (add) hipLaunchKernelGGL(k_wide_finish<true>, grid, dim3(256), 0, s, wide, A_hi, A_lo, count);
+    else hipLaunchKernelGGL(k_wide_finish<false>, grid, dim3(256), 0, s, wide, A_hi, A_lo, count);
     return hipGetLastError();
 }
 

@@ -1467,14 +1467,16 @@ int enqueue_run(fs_batch *b, hipStream_t s)
     if (b->o.reduction == FS_RED_DET)
         for (const SceneIn &sc : b->scenes)
             HIPCHECK(ctx, launch_fix_finish(s, sc.fix, sc.A_hi, sc.A_lo, (int64_t)sc.g.n * sc.E));
-    const int32_t add = b->o.zero_accumulators ? 0 : 1;
+    const bool add = !b->o.zero_accumulators;
     for (const SceneIn &sc : b->scenes) {
         const double *wide = b->wide ? (const double *)sc.fix : nullptr;
+        if (wide && (add || !sc.S)) {
+            HIPCHECK(ctx, launch_wide_finish(s, wide, sc.A_hi, sc.A_lo, (int64_t)sc.g.n * sc.E, add ? 1 : 0));
+            wide = nullptr;
+        }
         if (sc.S)
             HIPCHECK(ctx, launch_assign(s, sc.A_hi, sc.A_lo, sc.g.n, sc.E, sc.gamma, sc.S, sc.margin, ctx->status_dev,
-                                        wide, add));
-        else if (wide)
-            HIPCHECK(ctx, launch_wide_finish(s, wide, sc.A_hi, sc.A_lo, (int64_t)sc.g.n * sc.E, add));
+                                        wide));
     }
     return FS_OK;
 }

@@ -20,13 +20,13 @@ namespace {
 
 constexpr int kLdsDoubles = 2304;  // most staged doubles: 18 KiB, eight blocks per CU
 
-// WIDE: the rows come from the float64 totals `wide`; A_hi and A_lo are written
-// (added to, with `add`) on the way, and the labels use the values they then hold.
+// WIDE: the rows come from the float64 totals `wide`; A_hi and A_lo are set from them on the
+// way, and the labels use the values they then hold.
 template <bool WIDE>
 __global__ __launch_bounds__(256) void k_assign(float *__restrict__ A_hi, float *__restrict__ A_lo, int64_t n,
                                                 int32_t E, RowTile tl, float gamma, uint8_t *__restrict__ S,
                                                 float *__restrict__ margin, unsigned long long *__restrict__ status,
-                                                const double *__restrict__ wide, int32_t add)
+                                                const double *__restrict__ wide)
 {
     // as large as this launch needs, for more blocks per CU
     extern __shared__ double s_a[];
@@ -40,12 +40,10 @@ __global__ __launch_bounds__(256) void k_assign(float *__restrict__ A_hi, float 
     const bool vec = aligned16(A_hi) && aligned16(A_lo) && aligned16(wide);
     stage_rows(s_a, r0, R, E, tl, [&](int64_t i, int m, double (&v)[4]) {
         if constexpr (WIDE) {
-            double old[4] = {0.0, 0.0, 0.0, 0.0};
-            if (add) load_a4(A_hi, A_lo, vec, i, m, old);
             float hi[4], lo[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                wide_split(j < m ? old[j] + wide[i + j] : 0.0, hi[j], lo[j]);
+                wide_split(j < m ? wide[i + j] : 0.0, hi[j], lo[j]);
                 v[j] = (double)hi[j] + (double)lo[j];
             }
             if (vec && m == 4) {
@@ -118,7 +116,7 @@ __global__ __launch_bounds__(256) void k_assign(float *__restrict__ A_hi, float 
 }  // namespace
 
 hipError_t launch_assign(hipStream_t s, float *A_hi, float *A_lo, int64_t n, int32_t E, float gamma, uint8_t *S,
-                         float *margin, unsigned long long *status, const double *wide, int32_t add)
+                         float *margin, unsigned long long *status, const double *wide)
 {
     if (n == 0) return hipSuccess;
     const RowTile tl = row_tile(E, kLdsDoubles);
@@ -126,10 +124,10 @@ hipError_t launch_assign(hipStream_t s, float *A_hi, float *A_lo, int64_t n, int
     const size_t lds = (size_t)E * (tl.rows + 1) * 8 + (size_t)tl.rows * 12;
     if (wide)
         hipLaunchKernelGGL(k_assign<true>, dim3((unsigned)blocks), dim3(256), lds, s, A_hi, A_lo, n, E, tl, gamma, S,
-                           margin, status, wide, add);
+                           margin, status, wide);
     else
         hipLaunchKernelGGL(k_assign<false>, dim3((unsigned)blocks), dim3(256), lds, s, A_hi, A_lo, n, E, tl, gamma, S,
-                           margin, status, wide, add);
+                           margin, status, wide);
     return hipGetLastError();
 }
 

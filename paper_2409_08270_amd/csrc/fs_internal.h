@@ -289,7 +289,7 @@ hipError_t launch_accumulate(hipStream_t s, const float *rec, const uint32_t *va
 hipError_t launch_fix_finish(hipStream_t s, const unsigned long long *fix, float *A_hi, float *A_lo, int64_t count);
 
 // AccParams::wide: the float64 totals wide[i] (i < count) into A_hi and A_lo, added
-// to what they hold (add = 1) or in its place (add = 0)
+// to what they hold by atomics (add = 1) or in its place (add = 0)
 hipError_t launch_wide_finish(hipStream_t s, const double *wide, float *A_hi, float *A_lo, int64_t count, int32_t add);
 
 // a value as the float nearest to it and the float nearest to the remainder
@@ -300,9 +300,9 @@ __device__ __forceinline__ void wide_split(double v, float &hi, float &lo)
 }
 
 // with `wide`, A_hi and A_lo are first set from the float64 totals as
-// launch_wide_finish does (add as there), in the same pass over the rows
+// launch_wide_finish does (add = 0), in the same pass over the rows
 hipError_t launch_assign(hipStream_t s, float *A_hi, float *A_lo, int64_t n, int32_t E, float gamma, uint8_t *S,
-                         float *margin, unsigned long long *status, const double *wide = nullptr, int32_t add = 0);
+                         float *margin, unsigned long long *status, const double *wide = nullptr);
 
 // novel-view masks (fs_render.hip); memb is workspace of
 // render_member_bytes(n, E, mode) bytes (one word per group of objects and
