@@ -56,7 +56,8 @@ struct fs_ctx {
     DevBuf pk_alt, pv_alt, sort_ws, scan_ws;
     DevBuf items, items_k, items_k2, items_v2, items_ws;
     DevBuf fix;                // FS_RED_DET: the call's fixed-point totals
-    DevBuf memb;               // fs_render_masks: object membership bytes
+    DevBuf wide;               // float64 totals of a call; given back when memory is short
+    DevBuf memb;               // fs_render_masks: object membership words
     uint64_t items_tiles = 0;  // tile count the XCD-run table in `items` was built for
     Staging stage[kStaging];
     int stage_next = 0;
@@ -114,6 +115,14 @@ int alloc_buf(fs_ctx *ctx, DevBuf &b, size_t bytes)
     }
     if (hipMalloc(&b.p, bytes) != hipSuccess) {
         b.p = nullptr;
+        (void)hipGetLastError();  // left in place, it would be the next launch's error
+        if (&b != &ctx->wide && ctx->wide.p) {
+            // totals that a call can do without make room for what it needs
+            HIPCHECK(ctx, hipStreamSynchronize(ctx->stream));
+            HIPCHECK(ctx, hipFree(ctx->wide.p));
+            ctx->wide = DevBuf();
+            return alloc_buf(ctx, b, bytes);
+        }
         return set_err(ctx, FS_ERR_ALLOC, "device allocation of %zu bytes failed", bytes);
     }
     b.cap = bytes;
@@ -124,6 +133,14 @@ int ensure(fs_ctx *ctx, DevBuf &b, size_t bytes)
 {
     if (bytes <= b.cap && b.p) return FS_OK;
     return alloc_buf(ctx, b, bytes + bytes / 4 + 4096);
+}
+
+// ensure() of a workspace that the caller can do without: false, and no error, if there is no room
+bool try_ensure(fs_ctx *ctx, DevBuf &b, size_t bytes)
+{
+    if (ensure(ctx, b, bytes) == FS_OK) return true;
+    ctx->last_error[0] = 0;
+    return false;
 }
 
 void free_buf(DevBuf &b)
@@ -696,7 +713,7 @@ int fs_ctx_destroy(fs_ctx *ctx)
     (void)hipStreamSynchronize(ctx->stream);
     DevBuf *bufs[] = {&ctx->tables, &ctx->psegs, &ctx->dkeys, &ctx->dvals, &ctx->dkeys2, &ctx->dvals2, &ctx->counts, &ctx->offsets,
                       &ctx->pk_alt, &ctx->pv_alt, &ctx->sort_ws, &ctx->scan_ws, &ctx->items, &ctx->items_k,
-                      &ctx->items_k2, &ctx->items_v2, &ctx->items_ws, &ctx->fix, &ctx->memb};
+                      &ctx->items_k2, &ctx->items_v2, &ctx->items_ws, &ctx->fix, &ctx->wide, &ctx->memb};
     for (DevBuf *b : bufs) free_buf(*b);
     for (int i = 0; i < kStaging; ++i) {
         if (ctx->stage[i].host) (void)hipHostFree(ctx->stage[i].host);
@@ -870,43 +887,47 @@ int fs_accumulate(fs_ctx *ctx, const fs_proj *proj, const fs_bins *bins, const f
     if (proj->n == 0 || V == 0) return FS_OK;
     Plan pl;
     plan_add(pl, p, 0, proj->n, cams, 0, V, 0);
-    std::vector<SceneDev> sc{scene_dev(nullptr, proj->n, masks, A_hi, A_lo, n_classes)};
+    SceneDev sc = scene_dev(nullptr, proj->n, masks, A_hi, A_lo, n_classes);
     const int64_t n_fix = proj->n * (int64_t)n_classes;
     if (reduction == FS_RED_DET) {
         RCHECK(ensure(ctx, ctx->fix, (size_t)n_fix * 8));
         HIPCHECK(ctx, launch_fill_u32(ctx->stream, (uint32_t *)ctx->fix.p, 0u, 2 * n_fix));
-        sc[0].A_fix = (unsigned long long *)ctx->fix.p;
-    }
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIPCHECK(ctx, hipStreamIsCapturing(ctx->stream, &cap));
-    // float64 totals, unless the call is being captured (their workspace may have to
-    // grow) or there is no room for them
-    const bool wide = reduction == FS_RED_LDS2SUM && cap == hipStreamCaptureStatusNone && wide_pays(n_fix, pl.pixels) &&
-                      ensure(ctx, ctx->fix, (size_t)n_fix * 8) == FS_OK;
-    if (wide) {
-        HIPCHECK(ctx, launch_fill_u32(ctx->stream, (uint32_t *)ctx->fix.p, 0u, 2 * n_fix));
-        sc[0].A_fix = (unsigned long long *)ctx->fix.p;
+        sc.A_fix = (unsigned long long *)ctx->fix.p;
     }
     const SegDev lseg{0, (uint32_t)pl.tiles, 0, (uint32_t)pl.tiles, 0};
     Tables tabs;
-    const size_t views_at = tabs.add(pl.views), scenes_at = tabs.add(sc), lseg_at = tabs.add(&lseg, 1);
-    RCHECK(tabs.send(ctx));
-    const uint32_t *items = nullptr;
+    const size_t views_at = tabs.add(pl.views), scenes_at = tabs.add(&sc, 1), lseg_at = tabs.add(&lseg, 1);
+    RCHECK(ensure(ctx, ctx->tables, tabs.h.size()));
     if (p->tile_order == 0) {
         const size_t tb = (size_t)pl.tiles * 4;
-        const uint32_t lblocks = (uint32_t)((pl.tiles + kSortTile - 1) / kSortTile);
+        ctx->items_tiles = 0;  // the XCD-run table (tile_order 2) shares the buffer
         RCHECK(ensure(ctx, ctx->items, tb));
         RCHECK(ensure(ctx, ctx->items_k, tb));
         RCHECK(ensure(ctx, ctx->items_k2, tb));
         RCHECK(ensure(ctx, ctx->items_v2, tb));
-        RCHECK(ensure(ctx, ctx->items_ws, radix_ws_bytes(lblocks)));
-        ctx->items_tiles = 0;  // the XCD-run table (tile_order 2) shares the buffer
+        RCHECK(ensure(ctx, ctx->items_ws, radix_ws_bytes((uint32_t)((pl.tiles + kSortTile - 1) / kSortTile))));
+    } else if (p->tile_order == 2) {
+        RCHECK(build_xcd_items(ctx, pl.tiles));
+    }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIPCHECK(ctx, hipStreamIsCapturing(ctx->stream, &cap));
+    // float64 totals, unless the call is being captured (their workspace may have to
+    // grow) or there is no room for them: taken last, so that they stand in the way of nothing
+    const bool wide = reduction == FS_RED_LDS2SUM && cap == hipStreamCaptureStatusNone && wide_pays(n_fix, pl.pixels) &&
+                      try_ensure(ctx, ctx->wide, (size_t)n_fix * 8);
+    if (wide) {
+        HIPCHECK(ctx, launch_fill_u32(ctx->stream, (uint32_t *)ctx->wide.p, 0u, 2 * n_fix));
+        sc.A_fix = (unsigned long long *)ctx->wide.p;
+        memcpy(tabs.h.data() + scenes_at, &sc, sizeof(sc));
+    }
+    RCHECK(tabs.send(ctx));
+    const uint32_t *items = nullptr;
+    if (p->tile_order == 0) {
         RCHECK(enqueue_lpt(ctx, ctx->stream, bins->ranges, pl.tiles, table<SegDev>(ctx, lseg_at),
                            (uint32_t *)ctx->items.p, (uint32_t *)ctx->items_k.p, (uint32_t *)ctx->items_k2.p,
                            (uint32_t *)ctx->items_v2.p, ctx->items_ws.p));
         items = (const uint32_t *)ctx->items.p;
     } else if (p->tile_order == 2) {
-        RCHECK(build_xcd_items(ctx, pl.tiles));
         items = (const uint32_t *)ctx->items.p;
     }
     // events around the compositing launch alone (not under stream capture)
@@ -921,7 +942,7 @@ int fs_accumulate(fs_ctx *ctx, const fs_proj *proj, const fs_bins *bins, const f
     ctx->acc_timed = timed;
     if (reduction == FS_RED_DET)
         HIPCHECK(ctx, launch_fix_finish(ctx->stream, (const unsigned long long *)ctx->fix.p, A_hi, A_lo, n_fix));
-    if (wide) HIPCHECK(ctx, launch_wide_finish(ctx->stream, (const double *)ctx->fix.p, A_hi, A_lo, n_fix, 1));
+    if (wide) HIPCHECK(ctx, launch_wide_finish(ctx->stream, (const double *)ctx->wide.p, A_hi, A_lo, n_fix, 1));
     return FS_OK;
 }
 
@@ -1522,23 +1543,6 @@ int batch_build(fs_batch *b, const fs_scene *scenes, int32_t n_scenes)
         words += (int64_t)s.g.n * s.E;
         for (const fs_camera &c : s.cams) pixels += (uint64_t)c.width * (uint64_t)c.height;
     }
-    b->wide = b->o.reduction == FS_RED_LDS2SUM && words > 0 && wide_pays(words, pixels) &&
-              !sums_overlap(scenes, n_scenes);
-    // without room for the float64 totals the two-sum into A_hi and A_lo does as well
-    if (b->wide && batch_alloc(b, b->fix, (size_t)words * 8) != FS_OK) {
-        (void)hipGetLastError();
-        b->wide = false;
-    }
-    if (b->o.reduction == FS_RED_DET) RCHECK(batch_alloc(b, b->fix, (size_t)words * 8));
-    if (b->o.reduction == FS_RED_DET || b->wide) {
-        b->fix_words = words;
-        int64_t off = 0;
-        for (size_t i = 0; i < b->scenes.size(); ++i) {
-            b->scenes[i].fix = (unsigned long long *)b->fix.p + off;
-            sd[i].A_fix = b->scenes[i].fix;
-            off += (int64_t)b->scenes[i].g.n * b->scenes[i].E;
-        }
-    }
     RCHECK(batch_alloc(b, b->scenes_d, sd.size() * sizeof(SceneDev)));
     RCHECK(upload_vec(ctx, b->scenes_d, sd));
 
@@ -1771,6 +1775,23 @@ int batch_build(fs_batch *b, const fs_scene *scenes, int32_t n_scenes)
             RCHECK(batch_alloc(b, w.tile_done, ((size_t)b->max_tiles + 3) / 4 * 4 + 4));
             RCHECK(batch_alloc(b, w.live_table, (size_t)b->max_sat * 4));
         }
+    }
+    // the 64-bit totals come last: float64 ones only if everything else has its room (without them
+    // the two-sum into A_hi and A_lo does as well)
+    if (b->o.reduction == FS_RED_DET) RCHECK(batch_alloc(b, b->fix, (size_t)words * 8));
+    if (b->o.reduction == FS_RED_LDS2SUM && words > 0 && wide_pays(words, pixels) && !sums_overlap(scenes, n_scenes)) {
+        b->wide = batch_alloc(b, b->fix, (size_t)words * 8) == FS_OK;
+        if (!b->wide) ctx->last_error[0] = 0;
+    }
+    if (b->o.reduction == FS_RED_DET || b->wide) {
+        b->fix_words = words;
+        int64_t off = 0;
+        for (size_t i = 0; i < b->scenes.size(); ++i) {
+            b->scenes[i].fix = (unsigned long long *)b->fix.p + off;
+            sd[i].A_fix = b->scenes[i].fix;
+            off += (int64_t)b->scenes[i].g.n * b->scenes[i].E;
+        }
+        RCHECK(upload_vec(ctx, b->scenes_d, sd));
     }
     if (n_lanes > 1) {
         HIPCHECK(ctx, hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
