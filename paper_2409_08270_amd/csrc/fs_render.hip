@@ -147,22 +147,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 5))) voi
                     const float e = fmaf(q.w, dy, dx);
                     const float pw = fmaf(q.z * e, e, fmaf(q2.x * dy, dy, q2.y));
                     const float av = fminf(a_max, __builtin_amdgcn_exp2f(pw));
-                    // alpha = 0 leaves T, rho and the depth sum as they are
-                    const float alpha = on && pw >= q2.z && av >= P.alpha_min ? av : 0.0f;
+                    // alpha = 0 leaves T and rho as they are, and with z = 0 the depth sum (a
+                    // depth may be infinite)
+                    const bool hit = on && pw >= q2.z && av >= P.alpha_min;
+                    const float alpha = hit ? av : 0.0f, z = hit ? q2.w : 0.0f;
                     const float Tn = fmaf(-Tk, alpha, Tk);
                     const float wv = alpha * Tk;
                     const bool stop = alpha > 0.0f && Tn < P.t_min;  // the entry is not added, the pixel ends
                     if (__builtin_expect(__ballot(stop) != 0ull, 0)) {
                         if (!stop) {
                             rk = fmaf(alpha, Tk, rk);
-                            dk = fmaf(wv, q2.w, dk);
+                            dk = fmaf(wv, z, dk);
                             Tk = Tn;
                         }
                         on = on && !stop;
                         if (__ballot(on) == 0ull) break;
                     } else {
                         rk = fmaf(alpha, Tk, rk);
-                        dk = fmaf(wv, q2.w, dk);
+                        dk = fmaf(wv, z, dk);
                         Tk = Tn;
                     }
                 }
