@@ -206,7 +206,8 @@ def cameras(rows: np.ndarray):
     if rows.shape[0] == 0:
         return arr
     if not np.isfinite(rows[:, 16:18]).all():
-        raise ValueError("camera width and height must be finite")
+        bad = rows[:, 16:18][~np.isfinite(rows[:, 16:18])][0]
+        raise (ValueError if np.isnan(bad) else OverflowError)("camera width and height must be finite")
     # FsCamera is 16 floats and two int32; filled as a whole (field by field took 6 us a view)
     a = np.frombuffer(arr, np.float32).reshape(-1, 18)
     a[:, :16] = rows[:, :16]
