@@ -408,7 +408,8 @@ int fs_prompt_propagate(fs_ctx *ctx, const fs_gaussians *g, const fs_camera *cam
  * The buffers named in the scene descriptors are borrowed: they must stay
  * valid and keep their addresses until fs_batch_destroy. If the inputs change
  * so that a chunk needs more pairs than planned, the excess is dropped and
- * FS_DEV_PAIR_OVERFLOW is latched; create a new batch then. */
+ * FS_DEV_PAIR_OVERFLOW is latched; create a new batch then. A batch whose
+ * context has been destroyed can only be destroyed (FS_ERR_STATE otherwise). */
 typedef struct fs_batch fs_batch;
 
 /* Descriptors may name the same A_hi and A_lo (one scene's views or masks split

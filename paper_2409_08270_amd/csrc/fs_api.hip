@@ -42,8 +42,11 @@ constexpr int kQueueWord = 8;  // word of the context's npairs_dev block used as
 
 }  // namespace
 
+struct fs_batch;
+
 struct fs_ctx {
     hipStream_t stream = nullptr;
+    std::vector<fs_batch *> batches;  // created on this context and not destroyed
     int device = 0;
     unsigned long long *status_dev = nullptr;
     unsigned long long *status_host = nullptr;  // pinned, kStatusWords
@@ -582,6 +585,8 @@ bool sums_overlap(const fs_scene *scenes, int32_t n_scenes)
     return false;
 }
 
+void orphan_batches(fs_ctx *ctx);
+
 // FS_RED_DET: pixels per call (per scene in a batch); see to_fix's range
 constexpr uint64_t kFixMaxPixels = (uint64_t)1 << 29;
 
@@ -711,6 +716,7 @@ int fs_ctx_destroy(fs_ctx *ctx)
 {
     if (!ctx) return FS_ERR_ARG;
     (void)hipStreamSynchronize(ctx->stream);
+    orphan_batches(ctx);
     DevBuf *bufs[] = {&ctx->tables, &ctx->psegs, &ctx->dkeys, &ctx->dvals, &ctx->dkeys2, &ctx->dvals2, &ctx->counts, &ctx->offsets,
                       &ctx->pk_alt, &ctx->pv_alt, &ctx->sort_ws, &ctx->scan_ws, &ctx->items, &ctx->items_k,
                       &ctx->items_k2, &ctx->items_v2, &ctx->items_ws, &ctx->fix, &ctx->wide, &ctx->memb};
@@ -1298,6 +1304,13 @@ struct fs_batch {
 };
 
 namespace {
+
+// batches that outlive their context can only be destroyed
+void orphan_batches(fs_ctx *ctx)
+{
+    for (fs_batch *b : ctx->batches) b->ctx = nullptr;
+    ctx->batches.clear();
+}
 
 std::vector<DevBuf *> batch_bufs(fs_batch *b)
 {
@@ -1889,6 +1902,7 @@ int fs_batch_create(fs_ctx *ctx, const fs_scene *scenes, int32_t n_scenes, const
     fs_batch *b = new (std::nothrow) fs_batch();
     if (!b) return FS_ERR_ALLOC;
     b->ctx = ctx;
+    ctx->batches.push_back(b);
     b->p = *p;
     b->o = o;
     {
@@ -1911,6 +1925,7 @@ int fs_batch_run(fs_batch *b)
 {
     if (!b) return FS_ERR_ARG;
     fs_ctx *ctx = b->ctx;
+    if (!ctx) return FS_ERR_STATE;
     if (b->exec) {
         HIPCHECK(ctx, hipGraphLaunch(b->exec, ctx->stream));
         return FS_OK;
@@ -1925,6 +1940,7 @@ int fs_batch_accumulate_ms(fs_batch *b, float *total_ms, int32_t *n_launches)
 {
     if (!b || !total_ms || !n_launches) return FS_ERR_ARG;
     fs_ctx *ctx = b->ctx;
+    if (!ctx) return FS_ERR_STATE;
     if (!b->acc_recorded) return set_err(ctx, FS_ERR_STATE, "no fs_batch_run without a graph has been timed");
     double sum = 0.0;
     int32_t cnt = 0;
@@ -1950,6 +1966,7 @@ int fs_batch_chunk_lists(fs_batch *b, int32_t chunk, uint32_t *vals, int64_t val
 {
     if (!b || !info) return FS_ERR_ARG;
     fs_ctx *ctx = b->ctx;
+    if (!ctx) return FS_ERR_STATE;
     if (chunk < 0 || chunk >= (int32_t)b->chunks.size())
         return set_err(ctx, FS_ERR_ARG, "chunk %d of %zu", chunk, b->chunks.size());
     if (b->n_slabs != 1) return set_err(ctx, FS_ERR_STATE, "tile lists are per depth slab when depth_slabs > 1");
@@ -2000,7 +2017,11 @@ int fs_batch_get_info(fs_batch *b, fs_batch_info *out)
 int fs_batch_destroy(fs_batch *b)
 {
     if (!b) return FS_ERR_ARG;
-    if (b->ctx) (void)hipStreamSynchronize(b->ctx->stream);
+    if (b->ctx) {
+        (void)hipStreamSynchronize(b->ctx->stream);
+        std::vector<fs_batch *> &all = b->ctx->batches;
+        all.erase(std::remove(all.begin(), all.end(), b), all.end());
+    }
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
     for (Work &w : b->work) {

@@ -2,7 +2,7 @@
 (tests/native/hip_host.cpp: a limit on allocations, errors that stay until they are read, and the names
 of the kernels launched). The float64 totals of FS_RED_LDS2SUM are room that a call can do without:
 without them it composites by the two-sum (ACC_F32 = 0, not ACC_F64 = 2, in the kernel's name), and
-they never stand in the way of what a call or a batch needs.
+they never stand in the way of what a call or a batch needs. And the lifetimes of contexts and batches.
 
 Each case runs in a process of its own, where the stand-in is loaded before the library."""
 import ctypes
@@ -160,6 +160,23 @@ def case_batch_totals_come_last(h):
             assert h.fs.fs_batch_get_info(b, ctypes.byref(inf)) == 0
             assert ("k_wide_finish" in h.kernels()) == (extra >= TOTALS or h.lib.host_used() - used > room)
             h.fs.fs_batch_destroy(b)
+
+
+def case_a_batch_may_outlive_its_context(h):
+    h.ctx = h.context()
+    used = h.lib.host_used()
+    rc, b = h.batch()
+    rc2, b2 = h.batch()
+    assert rc == 0 and rc2 == 0 and h.fs.fs_batch_run(b) == 0
+    assert h.fs.fs_batch_destroy(b2) == 0
+    assert h.fs.fs_ctx_destroy(h.ctx) == 0
+    other = h.context()   # its memory is another context's now
+    assert h.fs.fs_batch_run(b) == h.L.FS_ERR_STATE
+    assert h.fs.fs_batch_accumulate_ms(b, ctypes.byref(ctypes.c_float()), ctypes.byref(ctypes.c_int32())) == h.L.FS_ERR_STATE
+    inf = h.L.FsChunkInfo()
+    assert h.fs.fs_batch_chunk_lists(b, 0, None, 0, None, 0, None, 0, ctypes.byref(inf)) == h.L.FS_ERR_STATE
+    assert h.fs.fs_batch_destroy(b) == 0
+    assert h.fs.fs_ctx_destroy(other) == 0 and h.lib.host_used() < used
 
 
 CASES = [c[5:] for c in dir() if c.startswith("case_")]
