@@ -6,13 +6,16 @@
 // into every view, giving the associated prompt of each view.
 //
 // One grid row (blockIdx.y) per prompt. A wave keeps its k smallest keys sorted across its lanes:
-// of 64 new keys only those below its k-th are taken, one by one, each by a ballot (its place) and
+// of 64 new keys those below its k-th are taken, one by one, each by a ballot (its place) and
 // a shift of the lanes above. The waves of a block merge their lists the same way; the second
 // kernel merges the blocks' lists of one prompt and looks at the k candidates in parallel.
 // What bounds it: latency (16 prompts on 200k centres read 2.4 MB from L2). A k-list per thread in
 // scratch memory with k block-wide minima per block, and the candidates one after the other, took
 // 165 + 57 us for 16 prompts, k = 10 and 200k centres; this takes 23 + 11 us
-// (64 prompts, k = 32 and 1M centres: 5290 + 395 us and 115 + 17 us).
+// (64 prompts, k = 32 and 1M centres: 5290 + 395 us and 115 + 17 us). Centres that lie in falling order
+// of their distance make every one a new nearest: one prompt on 1M of them took 124 us a call with the
+// thread's lists, 317 with waves that took each key in the order it came in, and takes 90 with the
+// rounds and lanes visited out of order (77 on centres in no order).
 //
 // Compiled without floating-point contraction: the distances and depths decide
 // which Gaussians are chosen, and they are evaluated in binary32 in a fixed
@@ -76,16 +79,28 @@ __device__ __forceinline__ void wave_take(unsigned long long &list, int k, unsig
     const int lane = threadIdx.x & 63;
     unsigned long long kth = read_lane(list, k - 1);
     unsigned long long todo = __ballot(key < kth);
-    while (todo) {
-        const int j = __ffsll((long long)todo) - 1;
-        todo &= todo - 1ull;
+    for (bool top = false; todo; top = !top) {  // from both ends: few are taken also if they rise or fall
+        const int j = top ? 63 - __clzll((long long)todo) : __ffsll((long long)todo) - 1;
         const unsigned long long c = read_lane(key, j);
-        if (c >= kth) continue;
         const int pos = __popcll(__ballot(list < c));
         const unsigned long long up = lane_before(list);
         list = lane < pos || lane >= k ? list : (lane == pos ? c : up);
         kth = read_lane(list, k - 1);
+        todo &= ~(1ull << j) & __ballot(key < kth);
     }
+}
+
+// Calls f(r) once for every r in [0, n), stepping through the range by the golden section. A
+// key below all those before it costs the wave an insertion, and centres that lie in the order
+// of their distance (falling with the index) would be inserted one by one: in this order only
+// about log n rounds hold nearer ones than those before.
+template <class F>
+__device__ __forceinline__ void golden_order(uint32_t n, F f)
+{
+    const uint32_t m = n > 1 ? 1u << (32 - __clz((int)(n - 1))) : n;  // a power of two, so any odd step visits all
+    const uint32_t step = (uint32_t)(((uint64_t)m * 2654435769u) >> 32) | 1u;
+    for (uint32_t i = 0, r = 0; i < m; ++i, r = (r + step) & (m - 1))
+        if (r < n) f(r);
 }
 
 // the waves' lists merged into that of wave 0
@@ -108,23 +123,25 @@ __global__ __launch_bounds__(256) void k_knn_partial(GaussPtrs g, int64_t n, Pro
     back_project(ref, pr[0], pr[1], pr[2], X, Y, Z);
     unsigned long long list = ~0ull;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    // four centres per lane in flight; the same number of rounds for every lane of a wave
-    for (int64_t w0 = i0 - (threadIdx.x & 63); w0 < n; w0 += 4 * stride) {
+    const int lane = threadIdx.x & 63;
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x - lane;  // the wave's
+    // four centres per lane in flight; the same rounds for every lane of a wave
+    golden_order(first < n ? (uint32_t)((n - first + 4 * stride - 1) / (4 * stride)) : 0u, [&](uint32_t r) {
+        const int64_t at = first + (int64_t)r * 4 * stride + lane;
         float x[4], y[4], z[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int64_t i = w0 + (threadIdx.x & 63) + q * stride;
+            const int64_t i = at + q * stride;
             x[q] = i < n ? g.mx[i] : 0.0f;
             y[q] = i < n ? g.my[i] : 0.0f;
             z[q] = i < n ? g.mz[i] : 0.0f;
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int64_t i = w0 + (threadIdx.x & 63) + q * stride;
+            const int64_t i = at + q * stride;
             wave_take(list, k, i < n ? dist_key(X, Y, Z, x[q], y[q], z[q], (uint32_t)i) : ~0ull);
         }
-    }
+    });
     block_merge(list, k, s_lists);
     if (threadIdx.x < (unsigned)k) part[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * k + threadIdx.x] = list;
 }
@@ -144,7 +161,11 @@ __global__ __launch_bounds__(256) void k_knn_final(const unsigned long long *__r
     out_uv += prompt * n_views * 2;
     out_vis += prompt * n_views;
     unsigned long long list = ~0ull;
-    for (int i = threadIdx.x - lane; i < n_part; i += blockDim.x) wave_take(list, k, i + lane < n_part ? part[i + lane] : ~0ull);
+    const int first = threadIdx.x - lane;
+    golden_order(first < n_part ? (uint32_t)((n_part - first + 255) / 256) : 0u, [&](uint32_t r) {
+        const int i = first + (int)r * 256 + lane;
+        wave_take(list, k, i < n_part ? part[i] : ~0ull);
+    });
     block_merge(list, k, s_lists);
     if (threadIdx.x < 64) {
         // among the k nearest centres, the one of least positive depth in the reference view
