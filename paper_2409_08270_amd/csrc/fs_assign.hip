@@ -11,18 +11,31 @@
 //
 // Memory: row tiles of fs_rows.h. What bounds it: HBM. 3M rows of 64 classes with margins move
 // 2.5 GB in 544 us, 4.6 TB/s (a copy reaches 4.75); with one element per lane and two divisions
-// each 800 us. Smaller tiles keep eight blocks on a CU: 4160 staged doubles instead of 2304 take
-// twice as long.
+// each 800 us. Small tiles keep seven or eight blocks on a CU: 4160 staged doubles take twice as long
+// as 2304. 2568 give 5, 9, 18 to 19, 36 to 39 and 70 to 77 classes the next larger tile: 1.5M rows of
+// 36 classes take 169 us (122 without margins) instead of 226 (183).
 #include "fs_rows.h"
 
 namespace fs {
 namespace {
 
-constexpr int kLdsDoubles = 2304;  // most staged doubles: 18 KiB, eight blocks per CU
+constexpr int kLdsDoubles = 2568;  // most staged doubles: 20 KiB, seven blocks per CU
+
+// log2 of the most groups of 4 rows per tile: 256 rows; fewer, down to 64, for a block on each of
+// 256 CUs, and 512 where 1024 blocks are left with them (with 2 classes 256 rows only fill half of a
+// block's threads: 1.5M rows with margins take 16.4 us instead of 27.7; with 512 rows 5000 rows
+// would take 5.8 us instead of 4.9)
+int32_t max_groups(int64_t n)
+{
+    int32_t g = n >= (1 << 19) ? 7 : 6;
+    while (g > 4 && n < ((int64_t)256 << (g + 2))) --g;
+    return g;
+}
 
 // WIDE: the rows come from the float64 totals `wide`; A_hi and A_lo are set from them on the
 // way, and the labels use the values they then hold.
-template <bool WIDE>
+// Rows are taken one per thread, in K rounds (tiles of at most 256 K rows).
+template <bool WIDE, int K>
 __global__ __launch_bounds__(256) void k_assign(float *__restrict__ A_hi, float *__restrict__ A_lo, int64_t n,
                                                 int32_t E, RowTile tl, float gamma, uint8_t *__restrict__ S,
                                                 float *__restrict__ margin, unsigned long long *__restrict__ status,
@@ -61,11 +74,14 @@ __global__ __launch_bounds__(256) void k_assign(float *__restrict__ A_hi, float 
             load_a4(A_hi, A_lo, vec, i, m, v);
         }
     });
-    if (tid < tl.rows) {
-        const double tot = row_total(s_a, tid, E, tl);
-        s_tot[tid] = tot;
-        s_members[tid] = 0;
-        const int r = ((tid & ((1 << tl.gsh) - 1)) << 2) + (tid >> tl.gsh);  // the row at position tid
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int pos = tid + 256 * k;
+        if (pos >= tl.rows) break;
+        const double tot = row_total(s_a, pos, E, tl);
+        s_tot[pos] = tot;
+        s_members[pos] = 0;
+        const int r = ((pos & ((1 << tl.gsh) - 1)) << 2) + (pos >> tl.gsh);  // the row at this position
         if (tot == 0.0 && r < R) atomicAdd(&s_cnt[0], 1u);
     }
     __syncthreads();
@@ -104,7 +120,9 @@ __global__ __launch_bounds__(256) void k_assign(float *__restrict__ A_hi, float 
     }
     if (low) atomicAdd(&s_cnt[2], low);
     __syncthreads();
-    if (tid < tl.rows && s_members[tid] > 1) atomicAdd(&s_cnt[1], 1u);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (tid + 256 * k < tl.rows && s_members[tid + 256 * k] > 1) atomicAdd(&s_cnt[1], 1u);
     __syncthreads();
     if (tid == 0) {
         if (s_cnt[0]) status_add(status, ST_UNSEEN, (unsigned long long)s_cnt[0]);
@@ -119,15 +137,15 @@ hipError_t launch_assign(hipStream_t s, float *A_hi, float *A_lo, int64_t n, int
                          float *margin, unsigned long long *status, const double *wide)
 {
     if (n == 0) return hipSuccess;
-    const RowTile tl = row_tile(E, kLdsDoubles);
+    const RowTile tl = row_tile(E, kLdsDoubles, max_groups(n));
     const int64_t blocks = (n + tl.rows - 1) / tl.rows;
     const size_t lds = (size_t)E * (tl.rows + 1) * 8 + (size_t)tl.rows * 12;
-    if (wide)
-        hipLaunchKernelGGL(k_assign<true>, dim3((unsigned)blocks), dim3(256), lds, s, A_hi, A_lo, n, E, tl, gamma, S,
-                           margin, status, wide);
-    else
-        hipLaunchKernelGGL(k_assign<false>, dim3((unsigned)blocks), dim3(256), lds, s, A_hi, A_lo, n, E, tl, gamma, S,
-                           margin, status, wide);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), lds, s, A_hi, A_lo, n, E, tl, gamma, S, margin, status,
+                           wide);
+    };
+    if (wide) go(tl.rows > 256 ? k_assign<true, 2> : k_assign<true, 1>);
+    else go(tl.rows > 256 ? k_assign<false, 2> : k_assign<false, 1>);
     return hipGetLastError();
 }
 

@@ -23,10 +23,10 @@ struct RowTile {
     int32_t rows;  // 4 << gsh
 };
 
-// Largest tile whose staged rows fit `doubles` of LDS: at most 256 rows, at least 4.
-inline RowTile row_tile(int32_t E, int32_t doubles)
+// Largest tile whose staged rows fit `doubles` of LDS: at most 4 << max_gsh rows, at least 4.
+inline RowTile row_tile(int32_t E, int32_t doubles, int32_t max_gsh = 6)
 {
-    RowTile t{6, 256};
+    RowTile t{max_gsh, 4 << max_gsh};
     while (t.gsh > 0 && (int64_t)E * (t.rows + 1) > doubles) {
         t.gsh -= 1;
         t.rows >>= 1;
