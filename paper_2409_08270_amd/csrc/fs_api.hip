@@ -1085,13 +1085,14 @@ int fs_diagnose(fs_ctx *ctx, const float *A_hi, const float *A_lo, const uint8_t
     const bool want_c = A_hi && contrib_hist, want_m = S && member_hist, want_o = S && gt && overlap;
     if (!want_c && !want_m && !want_o) return set_err(ctx, FS_ERR_ARG, "nothing to compute");
     const size_t E1 = (size_t)n_classes + 1, nw = 2 * E1 + 3 * (size_t)n_classes;
-    RCHECK(ensure(ctx, ctx->items_k, nw * 8 * kDiagStripes));
+    const int32_t stripes = diag_stripes(n, n_classes, (int64_t)nw);
+    RCHECK(ensure(ctx, ctx->items_k, nw * 8 * stripes));
     unsigned long long *d = (unsigned long long *)ctx->items_k.p;
-    HIPCHECK(ctx, launch_fill_u32(ctx->stream, (uint32_t *)d, 0u, (int64_t)nw * 2 * kDiagStripes));
+    HIPCHECK(ctx, launch_fill_u32(ctx->stream, (uint32_t *)d, 0u, (int64_t)nw * 2 * stripes));
     HIPCHECK(ctx, launch_diag_rows(ctx->stream, want_c ? A_hi : nullptr, want_c ? A_lo : nullptr,
                                    (want_m || want_o) ? S : nullptr, want_o ? gt : nullptr, n, n_classes,
-                                   (double)rel_eps, (int64_t)nw, d, d + E1, d + 2 * E1));
-    std::vector<uint64_t> h(nw * kDiagStripes);
+                                   (double)rel_eps, (int64_t)nw, stripes, d, d + E1, d + 2 * E1));
+    std::vector<uint64_t> h(nw * stripes);
     RCHECK(download(ctx, h.data(), d, h.size() * 8));
     for (size_t i = nw; i < h.size(); ++i) h[i % nw] += h[i];
     if (want_c) memcpy(contrib_hist, h.data(), E1 * 8);

@@ -8,7 +8,7 @@
 //   overlap[e]  |S_e and gt = e|, |S_e|, |gt = e| against per-Gaussian labels,
 //               from which a caller forms the IoU of each object.
 // One read of A, S and gt. A block works through several row tiles (fs_rows.h) and adds its
-// histograms once to one of kDiagStripes global copies (the host adds those up): atomics on one
+// histograms once to one of up to 8 global copies (the host adds those up): atomics on one
 // address take about 18 ns each, one after the other. A row tile's labels are read as dwords, 4 rows of one
 // object per lane; an object's members are counted from wave masks. 1M rows of 17 classes: 161 us
 // with a block per 240 rows and a row per thread, 48 us now (58 with 1792 blocks, which leave a CU
@@ -30,6 +30,7 @@ __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t x)
 __global__ __launch_bounds__(256) void k_diag_rows(const float *__restrict__ A_hi, const float *__restrict__ A_lo,
                                                    const uint8_t *__restrict__ S, const int32_t *__restrict__ gt,
                                                    int64_t n, int32_t E, RowTile tl, double rel_eps, int64_t stripe,
+                                                   int32_t n_stripes,
                                                    unsigned long long *__restrict__ contrib,
                                                    unsigned long long *__restrict__ member,
                                                    unsigned long long *__restrict__ overlap)
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(256) void k_diag_rows(const float *__restrict__ A_h
         }
     }
     __syncthreads();
-    const int64_t copy = stripe * (blockIdx.x % kDiagStripes);
+    const int64_t copy = stripe * (blockIdx.x % (uint32_t)n_stripes);
     for (int i = tid; i <= E; i += 256) {
         if (contrib && s_c[i]) atomicAdd(&contrib[copy + i], (unsigned long long)s_c[i]);
         if (member && s_m[i]) atomicAdd(&member[copy + i], (unsigned long long)s_m[i]);
@@ -107,19 +108,36 @@ __global__ __launch_bounds__(256) void k_diag_rows(const float *__restrict__ A_h
         if (overlap && s_o[i]) atomicAdd(&overlap[copy + i], (unsigned long long)s_o[i]);
 }
 
+unsigned diag_blocks(int64_t n, RowTile tl)
+{
+    const int64_t tiles = (n + tl.rows - 1) / tl.rows;
+    return (unsigned)(tiles < kDiagBlocks ? tiles : kDiagBlocks);
+}
+
 }  // namespace
 
+// The blocks queue at a copy's addresses, and every copy is cleared, read back and added up: the
+// two balance near copies^2 = 8 * blocks / words. Calls of 5000 rows (contributions alone, 256
+// classes, 625 blocks) take 40 us with 2 copies and 52 with 8, of 1.5M (17 classes, 4096 blocks)
+// 67 and 59.
+int32_t diag_stripes(int64_t n, int32_t E, int64_t words)
+{
+    const int64_t blocks = diag_blocks(n, row_tile(E, kDiagLds));
+    int32_t s = 1;
+    while (s < 8 && 4 * s * s * words <= 8 * blocks) s *= 2;
+    return s;
+}
+
 hipError_t launch_diag_rows(hipStream_t s, const float *A_hi, const float *A_lo, const uint8_t *S, const int32_t *gt,
-                            int64_t n, int32_t E, double rel_eps, int64_t stripe, unsigned long long *contrib,
-                            unsigned long long *member, unsigned long long *overlap)
+                            int64_t n, int32_t E, double rel_eps, int64_t stripe, int32_t n_stripes,
+                            unsigned long long *contrib, unsigned long long *member, unsigned long long *overlap)
 {
     if (n == 0) return hipSuccess;
     const RowTile tl = row_tile(E, kDiagLds);
-    const int64_t tiles = (n + tl.rows - 1) / tl.rows;
-    const unsigned blocks = (unsigned)(tiles < kDiagBlocks ? tiles : kDiagBlocks);
+    const unsigned blocks = diag_blocks(n, tl);
     const size_t lds = (size_t)E * (tl.rows + 1) * 8;
-    hipLaunchKernelGGL(k_diag_rows, dim3(blocks), dim3(256), lds, s, A_hi, A_lo, S, gt, n, E, tl, rel_eps, stripe, contrib,
-                       member, overlap);
+    hipLaunchKernelGGL(k_diag_rows, dim3(blocks), dim3(256), lds, s, A_hi, A_lo, S, gt, n, E, tl, rel_eps, stripe,
+                       n_stripes, contrib, member, overlap);
     return hipGetLastError();
 }
 

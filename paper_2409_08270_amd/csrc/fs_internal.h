@@ -314,13 +314,13 @@ hipError_t launch_render(hipStream_t s, const float *rec, const uint32_t *vals, 
 int64_t render_member_bytes(int64_t n, int32_t E, int32_t mode);
 
 // per-Gaussian diagnostics (fs_diag.hip): histograms [E+1] and overlap [E][3],
-// zeroed by the caller; each in kDiagStripes copies, `stripe` words apart, that the
-// caller adds up
+// zeroed by the caller; each in n_stripes copies (diag_stripes of the words of one copy),
+// `stripe` words apart, that the caller adds up
 constexpr int kMaxDiagE = 256;
-constexpr int kDiagStripes = 8;
+int32_t diag_stripes(int64_t n, int32_t E, int64_t words);
 hipError_t launch_diag_rows(hipStream_t s, const float *A_hi, const float *A_lo, const uint8_t *S, const int32_t *gt,
-                            int64_t n, int32_t E, double rel_eps, int64_t stripe, unsigned long long *contrib,
-                            unsigned long long *member, unsigned long long *overlap);
+                            int64_t n, int32_t E, double rel_eps, int64_t stripe, int32_t n_stripes,
+                            unsigned long long *contrib, unsigned long long *member, unsigned long long *overlap);
 
 // point-prompt propagation (fs_prompt.hip). prompts: device [n_prompts][3]
 // (px, py, depth); part: n_prompts * n_part_blocks * k keys; per prompt
