@@ -563,9 +563,15 @@ __global__ void k_xcd_items(uint32_t *items, uint32_t n_tiles)
 
 // FS_RED_LDS2SUM with float64 totals: one 64-bit atomic per (tile, Gaussian, label)
 // instead of a returning one into A_hi and one into A_lo, for a pass over the
-// n x E totals before and after. The line: a solve of 3M Gaussians x 64 classes
-// from 12 views of 1297x840 (n x E = 15 times the pixels) takes 28.9 ms either
-// way; one of 1M x 17 from 40 views (0.6 times) 17.4 against 20.3 ms.
+// n x E totals before and one after. The line, two-sum against totals in us:
+//   one view a call, 640x480, 200k Gaussians: 208/204 at 1.3 sums per pixel (2 classes), 429/379
+//   at 3.9 (6), 327/289 at 7.8 (12), 259/246 at 15.6 (24), 288/275 at 31; 50k Gaussians: 128/134
+//   at 7.8 (48 classes), 132/147 at 16; 3M in 1297x840: 379/371 at 5.5, 401/386 at 11, 434/471 at
+//   22; 2000 in 128x128: 62/65 at 0.24.
+//   batches: 850/810 at 3.9 (1M Gaussians, one view of 1008x756), 1120/990 at 7.8 (200k x 96
+//   classes, 8 views of 640x480), 940/845 at 15.8; those that add to A instead of replacing it gain
+//   half of that or nothing.
+// So most calls gain up to 8 and some lose beyond it.
 bool wide_pays(int64_t words, uint64_t pixels) { return (uint64_t)words <= 8 * pixels; }
 
 // Do the sums of two of the scenes (or A_hi and A_lo of one) share memory, as those of one scene
