@@ -217,7 +217,7 @@ __device__ __forceinline__ void accum_tile(const uint32_t tile, const float4 *__
     }
     if (tid < 8) s_bits[tid] = 0;
     if (tid < 4) s_wslots[tid] = 0;
-    if (tid == 0) s_tmajor = 0;
+    if (ACC == ACC_F32 && tid == 0) s_tmajor = 0;
     if (tid < 5) s_misc[tid] = 0;
     __syncthreads();
     if (inside && !active && (first || tstate == nullptr)) atomicAdd(&s_misc[0], 1u);  // counted once per solve
@@ -257,7 +257,8 @@ __device__ __forceinline__ void accum_tile(const uint32_t tile, const float4 *__
         }
         wmajor = uniform64(wmajor);
     }
-    if (lane == 0 && wmajor) atomicOr(&s_tmajor, wmajor);
+    if constexpr (ACC == ACC_F32)
+        if (lane == 0 && wmajor) atomicOr(&s_tmajor, wmajor);
     const bool minor = active && !plain && !((wmajor >> slot) & 1ull);
     const unsigned long long mmask = __ballot(minor);
     const bool wminor = mmask != 0ull;

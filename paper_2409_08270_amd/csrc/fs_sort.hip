@@ -265,6 +265,48 @@ __global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t *__restr
     hist[(int64_t)si.blk0 * 256 + (int64_t)d * si.bps + si.lb] = c;
 }
 
+// Rank of this lane's item among the wave's items of digit d so far: cnt (the wave's counts, in
+// LDS) plus the lanes below with the same digit; cnt then counts the wave's. dbits: width of d.
+__device__ __forceinline__ uint32_t wave_rank(uint32_t d, int dbits, uint32_t *cnt)
+{
+    const unsigned long long lt = (1ull << (threadIdx.x & 63)) - 1ull;
+    // lanes whose digit equals this lane's: for every bit, the lanes that
+    // agree with it are ~(ballot ^ m), m = all ones if the bit is set
+    // (one three-input bit operation per half of the 64-bit mask)
+    uint32_t plo = ~0u, phi = ~0u;
+#pragma unroll
+    for (int bit = 0; bit < 8; ++bit) {
+        if (bit >= dbits) break;
+        const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)d, (unsigned)bit, 1u);
+        const unsigned long long bb = __ballot(m != 0u);
+        plo &= ~((uint32_t)bb ^ m);
+        phi &= ~((uint32_t)(bb >> 32) ^ m);
+    }
+    const unsigned long long peers = ((unsigned long long)phi << 32) | plo;
+    const uint32_t before = cnt[d];
+    __builtin_amdgcn_wave_barrier();
+    if ((peers & lt) == 0ull) cnt[d] = before + (uint32_t)__popcll(peers);
+    __builtin_amdgcn_wave_barrier();
+    return before + (uint32_t)__popcll(peers & lt);
+}
+
+// From the waves' digit counts of a block tile: their prefixes over the waves (in place) and every
+// digit's start inside the tile. Returns the tile's count of digit threadIdx.x; ends with a barrier.
+__device__ __forceinline__ uint32_t digit_starts(uint32_t (&s_cnt)[kWaves][256], uint32_t (&s_dstart)[256], uint32_t *s_wsum)
+{
+    const int d = threadIdx.x;
+    uint32_t run = 0, tot;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) {
+        const uint32_t c = s_cnt[i][d];
+        s_cnt[i][d] = run;
+        run += c;
+    }
+    s_dstart[d] = block_excl_scan(run, s_wsum, tot);
+    __syncthreads();
+    return run;
+}
+
 // Stable scatter of one super-tile, block tile after block tile: wave w ranks
 // the contiguous items [w*1024, (w+1)*1024) of the block tile in 16 rounds of
 // 64, equal digits matched with 8 ballots; each digit's output cursor then
@@ -328,7 +370,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
         // segments' `out` are the same sums)
         s_gofs[threadIdx.x] = row[si.lb];
     }
-    const unsigned long long lt = (1ull << lane) - 1ull;
     const int dbits = 32 - __clz(dmask);  // digit width (dmask is 2^dbits - 1)
 
     for (int tb = 0; tb * kTile < si.nvalid; ++tb) {
@@ -340,24 +381,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 #pragma unroll
         for (int r = 0; r < kItems; ++r) {
             const uint32_t d = (key[r] >> shift) & dmask;
-            // lanes whose digit equals this lane's: for every bit, the lanes that
-            // agree with it are ~(ballot ^ m), m = all ones if the bit is set
-            // (one three-input bit operation per half of the 64-bit mask)
-            uint32_t plo = ~0u, phi = ~0u;
-#pragma unroll
-            for (int bit = 0; bit < 8; ++bit) {
-                if (bit >= dbits) break;
-                const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)d, (unsigned)bit, 1u);
-                const unsigned long long bb = __ballot(m != 0u);
-                plo &= ~((uint32_t)bb ^ m);
-                phi &= ~((uint32_t)(bb >> 32) ^ m);
-            }
-            const unsigned long long peers = ((unsigned long long)phi << 32) | plo;
-            const uint32_t before = s_cnt[w][d];
-            rnk[r] = before + (uint32_t)__popcll(peers & lt);
-            __builtin_amdgcn_wave_barrier();
-            if ((peers & lt) == 0ull) s_cnt[w][d] = before + (uint32_t)__popcll(peers);
-            __builtin_amdgcn_wave_barrier();
+            rnk[r] = wave_rank(d, dbits, s_cnt[w]);
         }
         __syncthreads();
         // the values come after the ranking, which would spill with them
@@ -370,23 +394,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
                 val[r] = li < nvalid ? vin[base + li] : 0u;
             }
         }
-        // per-digit totals, wave prefixes and the digit starts inside the block tile
-        uint32_t tile_count;
-        {
-            const int d = threadIdx.x;
-            uint32_t run = 0;
-#pragma unroll
-            for (int i = 0; i < kWaves; ++i) {
-                const uint32_t c = s_cnt[i][d];
-                s_cnt[i][d] = run;
-                run += c;
-            }
-            uint32_t tot;
-            const uint32_t ex = block_excl_scan(run, s_wsum, tot);
-            s_dstart[d] = ex;
-            tile_count = run;
-        }
-        __syncthreads();
+        const uint32_t tile_count = digit_starts(s_cnt, s_dstart, s_wsum);
 #pragma unroll
         for (int r = 0; r < kItems; ++r) {
             const uint32_t d = (key[r] >> shift) & dmask;
@@ -435,7 +443,6 @@ __global__ __launch_bounds__(kThreads) void k_sort_block(const uint32_t *kin, co
     __shared__ uint32_t s_k[kTile], s_v[kTile];
     const SegInfo si = seg_of_block(segs, n_segs, blockIdx.x, len_dev, 1, 0);
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, n = si.nvalid;
-    const unsigned long long lt = (1ull << lane) - 1ull;
     const int rounds = (n + kThreads - 1) / kThreads;  // items per thread that are used
     uint32_t key[kItems], val[kItems];
     // wave w holds items [w * 64 * rounds, (w + 1) * 64 * rounds), 64 per round
@@ -456,35 +463,10 @@ __global__ __launch_bounds__(kThreads) void k_sort_block(const uint32_t *kin, co
             if (r >= rounds) break;
             // items past the end rank behind every other of their digit: they come last
             const uint32_t d = (key[r] >> shift) & 255u;
-            uint32_t plo = ~0u, phi = ~0u;
-#pragma unroll
-            for (int bit = 0; bit < 8; ++bit) {
-                const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)d, (unsigned)bit, 1u);
-                const unsigned long long bb = __ballot(m != 0u);
-                plo &= ~((uint32_t)bb ^ m);
-                phi &= ~((uint32_t)(bb >> 32) ^ m);
-            }
-            const unsigned long long peers = ((unsigned long long)phi << 32) | plo;
-            const uint32_t before = s_cnt[w][d];
-            rnk[r] = before + (uint32_t)__popcll(peers & lt);
-            __builtin_amdgcn_wave_barrier();
-            if ((peers & lt) == 0ull) s_cnt[w][d] = before + (uint32_t)__popcll(peers);
-            __builtin_amdgcn_wave_barrier();
+            rnk[r] = wave_rank(d, 8, s_cnt[w]);
         }
         __syncthreads();
-        {
-            const int d = threadIdx.x;
-            uint32_t run = 0;
-#pragma unroll
-            for (int i = 0; i < kWaves; ++i) {
-                const uint32_t c = s_cnt[i][d];
-                s_cnt[i][d] = run;
-                run += c;
-            }
-            uint32_t tot;
-            s_dstart[d] = block_excl_scan(run, s_wsum, tot);
-        }
-        __syncthreads();
+        digit_starts(s_cnt, s_dstart, s_wsum);
 #pragma unroll
         for (int r = 0; r < kItems; ++r) {
             if (r >= rounds) break;
@@ -505,7 +487,7 @@ __global__ __launch_bounds__(kThreads) void k_sort_block(const uint32_t *kin, co
     for (int r = 0; r < kItems; ++r) {
         const int i = first + r * 64;
         if (r < rounds && i < n) {
-            if (kout) kout[si.base + i] = key[r];
+            kout[si.base + i] = key[r];
             vout[si.base + i] = val[r];
         }
     }
@@ -619,27 +601,6 @@ __global__ __launch_bounds__(kThreads) void k_live_table(const ViewDev *__restri
     }
 }
 
-// Inclusive sum of x over the block's threads; *total receives the block sum.
-__device__ __forceinline__ uint32_t block_scan_incl(uint32_t x, uint32_t *s_wsum, uint32_t *total)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(x, off);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) s_wsum[w] = x;
-    __syncthreads();
-    uint32_t t = 0;
-    for (int k = 0; k < kWaves; ++k) {
-        if (k < w) x += s_wsum[k];
-        t += s_wsum[k];
-    }
-    *total = t;
-    __syncthreads();
-    return x;
-}
-
 // Emission of the (tile, Gaussian) pairs. Block b handles the depth-sorted
 // elements [256 b, 256 b + 256), whose outputs form one contiguous range from
 // offsets[256 b]. Splats differ widely in their number of tile rows and of
@@ -722,7 +683,7 @@ __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t *__restrict__ 
     }
     if constexpr (COUNT) s_cnt[tid] = cnt;
     uint32_t n_rows = 0;
-    const uint32_t incl = block_scan_incl(rows, s_wsum, &n_rows);
+    const uint32_t incl = block_excl_scan(rows, s_wsum, n_rows) + rows;
     s_roff[tid + 1] = incl;
     if (tid == 0) s_roff[0] = 0;
     for (uint32_t r = incl - rows; r < min(incl, kRowMap); ++r) s_rowelem[r] = (uint8_t)tid;
@@ -765,7 +726,7 @@ __global__ __launch_bounds__(kThreads) void k_emit(const uint32_t *__restrict__ 
         }
         if constexpr (COUNT) continue;
         uint32_t round_total = 0;
-        const uint32_t ex = block_scan_incl(n, s_wsum, &round_total) - n;
+        const uint32_t ex = block_excl_scan(n, s_wsum, round_total);
         uint32_t p = lo + carry + ex;
         uint32_t g = 0, rowbase = 0, outbase = 0;
         if (n > 0) {
@@ -1011,11 +972,10 @@ hipError_t radix_sort(hipStream_t s, uint32_t *keys, uint32_t *vals, uint32_t *k
 {
     if (n_blocks == 0 || n_segs == 0) return hipSuccess;
     if (tpb < 1) return hipErrorInvalidValue;
-    if (max_len <= (uint64_t)kTile && max_len > 0 && key_count == nullptr) {
+    if (max_len <= (uint64_t)kTile && max_len > 0 && key_count == nullptr && last_keys) {
         const bool odd = ((bits + 7) / 8) % 2 == 1;
-        hipLaunchKernelGGL(k_sort_block, dim3(n_blocks), dim3(kThreads), 0, s, keys, vals,
-                           last_keys ? (odd ? keys_alt : keys) : nullptr, odd ? vals_alt : vals, segs, n_segs, bits,
-                           len_dev);
+        hipLaunchKernelGGL(k_sort_block, dim3(n_blocks), dim3(kThreads), 0, s, keys, vals, odd ? keys_alt : keys,
+                           odd ? vals_alt : vals, segs, n_segs, bits, len_dev);
         return hipGetLastError();
     }
     const int64_t hist_n = (int64_t)n_blocks * 256;
