@@ -193,8 +193,8 @@ int fs_status_get(fs_ctx *ctx, fs_status *out, int32_t clear);
 
 /* Duration in ms of the last compositing kernel that fs_accumulate launched on
  * this context, from HIP events recorded on the context's stream right before
- * and after that launch (the work-order sort and the host's checks are
- * outside). Waits for the launch to finish. FS_ERR_ARG if no fs_accumulate
+ * and after that launch (the work-order sort, the host's checks and, with 64-bit
+ * totals, clearing them and adding them into A are outside). Waits for the launch to finish. FS_ERR_ARG if no fs_accumulate
  * call has been timed (calls made under stream capture are not). */
 int fs_last_accumulate_ms(fs_ctx *ctx, float *ms);
 
@@ -263,8 +263,10 @@ int fs_accumulate(fs_ctx *ctx, const fs_proj *proj, const fs_bins *bins, const f
 
 /* fs_accumulate for callers that cannot allocate memory: code recorded under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * Same arguments, results and errors as fs_accumulate; the call itself
- * allocates nothing (no hipMalloc, hipFree or host allocation). Its device
+ * Same arguments and errors as fs_accumulate, and the same results but for one
+ * thing: FS_RED_LDS2SUM always adds weight by weight here (no float64 totals), so
+ * that A_hi and A_lo split the sum otherwise and it may differ by its rounding.
+ * The call itself allocates nothing (no hipMalloc, hipFree or host allocation). Its device
  * workspace (the call's view table, the longest-list-first work order and
  * that order's sort workspace) is one static array of about 17.5 MB per GPU
  * (each GPU the library runs on holds it until the process ends); its host
