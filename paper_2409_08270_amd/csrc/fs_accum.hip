@@ -32,6 +32,11 @@
 // about one rounding; the partials of labels that only appear as stray pixels in
 // a tile (relabel noise) are small and go to A_lo directly.
 //
+// What bounds the kernel now: vector issue. On 32 scenes (8.6M Gaussians, 2,327 views up to
+// 1008x756; 21 launches of 4.95 ms, 6.88 before the totals) the SIMDs issue vector instructions in
+// 0.85 of their cycles, 27 per list entry and wave of which 14 are the step itself, with 5.8 of 7
+// waves resident. A call of few tiles instead waits for its longest list.
+//
 // Bit-reproducible sums (FS_RED_DET). Atomic float additions round in whatever
 // order they arrive. In this mode every label of a wave is summed by the
 // reduce-scatter (a fixed butterfly, so the same bits on every run), each such

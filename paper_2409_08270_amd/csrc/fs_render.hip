@@ -20,15 +20,18 @@
 // each). Each object's arithmetic is the same sequence of operations as compositing
 // it alone.
 //
-// What bounds it: VALU issue of the steps (about 17 instructions per entry that
-// reaches the block) and, with many objects, the walks. Having every pixel walk all
-// the tile's entries of any of 8 objects, with a barrier per 256 entries and a
-// divergent branch per object, took 13.5 ms for 8 views of 800x600 of a
-// 500k-Gaussian scene with 10 classes; this takes 1.85 ms. 16 objects a walk: with 8
-// the same scene takes 2.4 ms and 4 views of 1008x756 of 1M Gaussians with 64 classes
-// 15.1 ms against 9.1 ms; with 32 the state of the objects (three registers each)
-// leaves two waves per SIMD, 3.3 and 14.4 ms. Five waves per SIMD (96 registers, 16
-// spilled outside the steps) against four: 1.85 and 2.04 ms.
+// What bounds it: the chain of the steps (two LDS reads, then 21 vector and 16 scalar
+// instructions per entry and object, most of them one after the other) with too few waves to
+// hide it, as tiles differ in their lists. Counters: vector issue in 0.42 of the SIMDs' cycles
+// and 2.7 of 5 waves resident for 8 views of 800x600 of a 500k-Gaussian scene with 10 classes
+// (1.90 ms), 0.55 and 3.8 for 40 views of 1008x756 of 700k Gaussians (9.45 ms). Having every
+// pixel walk all the tile's entries of any of 8 objects, with a barrier per 256 entries and a
+// divergent branch per object, took 13.5 ms for the 8 views. 16 objects a walk: with 8 the same
+// scene takes 2.4 ms and 4 views of 1008x756 of 1M Gaussians with 64 classes 15.1 ms against
+// 9.1 ms; with 32 the state of the objects (three registers each) leaves two waves per SIMD, 3.3
+// and 14.4 ms. Five waves per SIMD (96 registers, 16 spilled outside the steps) against four: 1.85
+// and 2.04 ms (these before the depth of an entry that a lane does not take was left out of
+// its sum, which took the 1.85 to 1.90).
 //
 // The steps are per (entry, object), so Gaussians in many objects at once cost more than
 // they would with one walk that forms an alpha for all of them: 4 views of 800x600 of 300k
