@@ -7,7 +7,7 @@
 namespace fs {
 namespace {
 
-constexpr int kSweepLds = 4160;       // doubles of staged rows
+constexpr int kSweepLds = 4352;       // doubles of staged rows
 constexpr int kSweepCounters = 4096;  // n_gamma * E counters per block
 
 // S[k][t][g] = a_n > o_n + gamma_k for every gamma of the sweep, from one read
@@ -15,10 +15,15 @@ constexpr int kSweepCounters = 4096;  // n_gamma * E counters per block
 // (counts may be NULL). Row tiles of fs_rows.h: a thread holds 4 rows of one object
 // and writes a dword per bias. A comparison's result is a wave-wide mask, so an object's
 // members are counted with scalar bit counts of its lanes' part of the masks.
-// What bounds it: the comparisons (float64, one per label) and the label bytes, 448 MB in 180 us
+// What bounds it: the comparisons (float64, one per label) and the label bytes, 448 MB in 158 us
 // for 700k rows, 10 classes and 64 biases (560 us with one byte per lane and store). Larger tiles
-// than the assignment's (4160 doubles) give each wave one object up to 16 classes, so that its
-// members are counted by scalar instructions: 228 against 273 us a call with 2304.
+// than the assignment's give each wave one object up to 16 classes, so that its members are counted
+// by scalar instructions: 228 against 273 us a call with 2304 doubles; 4352 of them leave 16 rows at 256
+// classes. With many classes a wave writes runs of 16 to 64 bytes of many label rows, and neighbouring
+// tiles complete each other's lines: with tiles taken in turn by the XCDs those lines went to memory
+// in parts, 700k rows of 128 classes and 32 biases 5.8 ms, 256 and 16 10.4 ms (2.7 and 4.2 with one
+// row per lane); in runs of tiles per XCD 2.0 and 2.5 ms, and 64 classes x 64 biases 1.4 ms instead
+// of 2.2.
 __global__ __launch_bounds__(256) void k_assign_sweep(const float *__restrict__ A_hi, const float *__restrict__ A_lo,
                                                       int64_t n, int32_t E, RowTile tl,
                                                       const float *__restrict__ gammas, int32_t n_gamma,
@@ -30,7 +35,7 @@ __global__ __launch_bounds__(256) void k_assign_sweep(const float *__restrict__ 
     uint32_t *const s_cnt = reinterpret_cast<uint32_t *>(s_a + E * (tl.rows + 1));
     __shared__ double s_tot[256];
     __shared__ double s_g[64];
-    const int64_t r0 = (int64_t)blockIdx.x * tl.rows;
+    const int64_t r0 = tile_of_block() * tl.rows;
     const int R = (int)min((int64_t)tl.rows, n - r0);
     const int tid = threadIdx.x, rs = tl.rows + 1;
     if (counts)
