@@ -28,7 +28,7 @@
 // hide it, as tiles differ in their lists; in large scenes the reading of the entries. Having
 // every pixel walk all the tile's entries of any of 8 objects, with a barrier per 256 entries and
 // a divergent branch per object, took 13.5 ms for 8 views of 800x600 of a 500k-Gaussian scene with
-// 10 classes; this takes 1.88. 16 objects a walk: with 8 the same scene takes 2.4 ms and 4 views
+// 10 classes; this takes 1.85. 16 objects a walk: with 8 the same scene takes 2.4 ms and 4 views
 // of 1008x756 of 1M Gaussians with 64 classes 15.1 ms against 9.1 ms (5.5 shared); with 32 the
 // state of the objects (three registers each) leaves two waves per SIMD, 3.3 and 14.4 ms. Waves on
 // their own: five per SIMD (96 registers, 16 spilled outside the steps) against four, 1.85 and
