@@ -12,6 +12,8 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -42,11 +44,12 @@ constexpr int kQueueWord = 8;  // word of the context's npairs_dev block used as
 
 }  // namespace
 
-struct fs_batch;
+// where a batch finds its context; nullptr once that is destroyed
+using CtxLink = std::shared_ptr<std::atomic<fs_ctx *>>;
 
 struct fs_ctx {
     hipStream_t stream = nullptr;
-    std::vector<fs_batch *> batches;  // created on this context and not destroyed
+    CtxLink link;  // of its batches, from the first one on
     int device = 0;
     unsigned long long *status_dev = nullptr;
     unsigned long long *status_host = nullptr;  // pinned, kStatusWords
@@ -591,8 +594,6 @@ bool sums_overlap(const fs_scene *scenes, int32_t n_scenes)
     return false;
 }
 
-void orphan_batches(fs_ctx *ctx);
-
 // FS_RED_DET: pixels per call (per scene in a batch); see to_fix's range
 constexpr uint64_t kFixMaxPixels = (uint64_t)1 << 29;
 
@@ -722,7 +723,7 @@ int fs_ctx_destroy(fs_ctx *ctx)
 {
     if (!ctx) return FS_ERR_ARG;
     (void)hipStreamSynchronize(ctx->stream);
-    orphan_batches(ctx);
+    if (ctx->link) ctx->link->store(nullptr);  // batches may outlive it, and can then only be destroyed
     DevBuf *bufs[] = {&ctx->tables, &ctx->psegs, &ctx->dkeys, &ctx->dvals, &ctx->dkeys2, &ctx->dvals2, &ctx->counts, &ctx->offsets,
                       &ctx->pk_alt, &ctx->pv_alt, &ctx->sort_ws, &ctx->scan_ws, &ctx->items, &ctx->items_k,
                       &ctx->items_k2, &ctx->items_v2, &ctx->items_ws, &ctx->fix, &ctx->wide, &ctx->memb};
@@ -1285,7 +1286,8 @@ struct Work {
 };
 
 struct fs_batch {
-    fs_ctx *ctx = nullptr;
+    CtxLink link;
+    fs_ctx *ctx() const { return link->load(); }
     fs_params p;
     fs_batch_opts o;
     std::vector<SceneIn> scenes;
@@ -1311,13 +1313,6 @@ struct fs_batch {
 };
 
 namespace {
-
-// batches that outlive their context can only be destroyed
-void orphan_batches(fs_ctx *ctx)
-{
-    for (fs_batch *b : ctx->batches) b->ctx = nullptr;
-    ctx->batches.clear();
-}
 
 std::vector<DevBuf *> batch_bufs(fs_batch *b)
 {
@@ -1356,7 +1351,7 @@ void chunk_plan(fs_batch *b, Chunk &c)
 // projection and per-view depth sort of one chunk
 int enqueue_front(fs_batch *b, Work &w, Chunk &c, hipStream_t s)
 {
-    fs_ctx *ctx = b->ctx;
+    fs_ctx *ctx = b->ctx();
     const Plan &pl = c.plan;
     if (pl.elems == 0) return FS_OK;
     uint32_t *dk = (uint32_t *)w.dkeys.p, *dv = (uint32_t *)w.dvals.p;
@@ -1374,7 +1369,7 @@ int enqueue_front(fs_batch *b, Work &w, Chunk &c, hipStream_t s)
 // pair counts of every element (no slab, no culling) and their exclusive scan; total into *np
 int enqueue_full_count(fs_batch *b, Work &w, Chunk &c, uint32_t *np, hipStream_t s)
 {
-    fs_ctx *ctx = b->ctx;
+    fs_ctx *ctx = b->ctx();
     const Plan &pl = c.plan;
     const int64_t total = (int64_t)pl.elems;
     if (total == 0) {
@@ -1395,7 +1390,7 @@ int enqueue_full_count(fs_batch *b, Work &w, Chunk &c, uint32_t *np, hipStream_t
 // later slabs, so the long tails of dense tiles are never sorted.
 int enqueue_slabs(fs_batch *b, Work &w, Chunk &c, int chunk_idx, hipStream_t s, bool composite = true)
 {
-    fs_ctx *ctx = b->ctx;
+    fs_ctx *ctx = b->ctx();
     const Plan &pl = c.plan;
     const int64_t total = (int64_t)pl.elems;
     const int32_t V = (int32_t)pl.views.size();
@@ -1476,7 +1471,7 @@ int enqueue_slabs(fs_batch *b, Work &w, Chunk &c, int chunk_idx, hipStream_t s, 
 // the whole solve: optional zeroing, every chunk, every scene's assignment
 int enqueue_run(fs_batch *b, hipStream_t s)
 {
-    fs_ctx *ctx = b->ctx;
+    fs_ctx *ctx = b->ctx();
     if (b->o.zero_accumulators && !b->wide) {  // the float64 totals replace A at the end
         for (const SceneIn &sc : b->scenes) {
             const int64_t cnt = (int64_t)sc.g.n * sc.E;
@@ -1524,14 +1519,14 @@ int enqueue_run(fs_batch *b, hipStream_t s)
 
 int batch_alloc(fs_batch *b, DevBuf &buf, size_t bytes)
 {
-    RCHECK(alloc_buf(b->ctx, buf, bytes < 256 ? 256 : bytes));
+    RCHECK(alloc_buf(b->ctx(), buf, bytes < 256 ? 256 : bytes));
     b->ws_bytes += (int64_t)buf.cap;
     return FS_OK;
 }
 
 int batch_build(fs_batch *b, const fs_scene *scenes, int32_t n_scenes)
 {
-    fs_ctx *ctx = b->ctx;
+    fs_ctx *ctx = b->ctx();
     const int64_t pair_budget = b->o.pair_budget > 0 ? b->o.pair_budget : (int64_t)1 << 28;
     const int64_t elem_budget = b->o.elem_budget > 0 ? b->o.elem_budget : (int64_t)1 << 26;
     // scenes
@@ -1908,8 +1903,8 @@ int fs_batch_create(fs_ctx *ctx, const fs_scene *scenes, int32_t n_scenes, const
     if (o.reduction == FS_RED_LDS2SUM && !all_lo) return set_err(ctx, FS_ERR_ARG, "FS_RED_LDS2SUM needs A_lo in every scene");
     fs_batch *b = new (std::nothrow) fs_batch();
     if (!b) return FS_ERR_ALLOC;
-    b->ctx = ctx;
-    ctx->batches.push_back(b);
+    if (!ctx->link) ctx->link = std::make_shared<std::atomic<fs_ctx *>>(ctx);
+    b->link = ctx->link;
     b->p = *p;
     b->o = o;
     {
@@ -1931,7 +1926,7 @@ int fs_batch_create(fs_ctx *ctx, const fs_scene *scenes, int32_t n_scenes, const
 int fs_batch_run(fs_batch *b)
 {
     if (!b) return FS_ERR_ARG;
-    fs_ctx *ctx = b->ctx;
+    fs_ctx *ctx = b->ctx();
     if (!ctx) return FS_ERR_STATE;
     if (b->exec) {
         HIPCHECK(ctx, hipGraphLaunch(b->exec, ctx->stream));
@@ -1946,7 +1941,7 @@ int fs_batch_run(fs_batch *b)
 int fs_batch_accumulate_ms(fs_batch *b, float *total_ms, int32_t *n_launches)
 {
     if (!b || !total_ms || !n_launches) return FS_ERR_ARG;
-    fs_ctx *ctx = b->ctx;
+    fs_ctx *ctx = b->ctx();
     if (!ctx) return FS_ERR_STATE;
     if (!b->acc_recorded) return set_err(ctx, FS_ERR_STATE, "no fs_batch_run without a graph has been timed");
     double sum = 0.0;
@@ -1972,7 +1967,7 @@ int fs_batch_chunk_lists(fs_batch *b, int32_t chunk, uint32_t *vals, int64_t val
                          int64_t ranges_cap, int32_t *view_refs, int32_t refs_cap, fs_chunk_info *info)
 {
     if (!b || !info) return FS_ERR_ARG;
-    fs_ctx *ctx = b->ctx;
+    fs_ctx *ctx = b->ctx();
     if (!ctx) return FS_ERR_STATE;
     if (chunk < 0 || chunk >= (int32_t)b->chunks.size())
         return set_err(ctx, FS_ERR_ARG, "chunk %d of %zu", chunk, b->chunks.size());
@@ -2024,11 +2019,7 @@ int fs_batch_get_info(fs_batch *b, fs_batch_info *out)
 int fs_batch_destroy(fs_batch *b)
 {
     if (!b) return FS_ERR_ARG;
-    if (b->ctx) {
-        (void)hipStreamSynchronize(b->ctx->stream);
-        std::vector<fs_batch *> &all = b->ctx->batches;
-        all.erase(std::remove(all.begin(), all.end(), b), all.end());
-    }
+    if (fs_ctx *ctx = b->ctx()) (void)hipStreamSynchronize(ctx->stream);
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
     for (Work &w : b->work) {

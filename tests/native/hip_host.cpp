@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -15,7 +16,8 @@ std::map<const void *, std::string> g_kernels;
 std::vector<std::string> g_launched;
 std::map<void *, size_t> g_blocks;
 size_t g_limit = ~(size_t)0, g_used = 0, g_peak = 0;
-int g_last = 0;
+thread_local int g_last = 0;
+std::mutex g_mu;  // of all the above
 
 int fail(int code) { return g_last = code; }
 }  // namespace
@@ -63,6 +65,7 @@ int __hipPushCallConfiguration(dim3_t, dim3_t, size_t, void *) { return 0; }
 int __hipPopCallConfiguration(dim3_t *, dim3_t *, size_t *, void **) { return 0; }
 int hipLaunchKernel(const void *f, dim3_t, dim3_t, void **, size_t, void *)
 {
+    std::lock_guard<std::mutex> l(g_mu);
     g_launched.push_back(g_kernels[f]);
     return 0;
 }
@@ -70,6 +73,7 @@ int hipLaunchKernel(const void *f, dim3_t, dim3_t, void **, size_t, void *)
 // ---- memory
 int hipMalloc(void **p, size_t bytes)
 {
+    std::lock_guard<std::mutex> l(g_mu);
     *p = nullptr;
     if (bytes > g_limit || g_used > g_limit - bytes) return fail(2);  // hipErrorOutOfMemory
     *p = calloc(1, bytes ? bytes : 1);
@@ -81,6 +85,7 @@ int hipMalloc(void **p, size_t bytes)
 int hipFree(void *p)
 {
     if (!p) return 0;
+    std::lock_guard<std::mutex> l(g_mu);
     const auto it = g_blocks.find(p);
     if (it == g_blocks.end()) return fail(1);
     g_used -= it->second;

@@ -7,8 +7,10 @@ they never stand in the way of what a call or a batch needs. And the lifetimes o
 Each case runs in a process of its own, where the stand-in is loaded before the library."""
 import ctypes
 import os
+import queue
 import subprocess
 import sys
+import threading
 import types
 
 import numpy as np
@@ -177,6 +179,33 @@ def case_a_batch_may_outlive_its_context(h):
     assert h.fs.fs_batch_chunk_lists(b, 0, None, 0, None, 0, None, 0, ctypes.byref(inf)) == h.L.FS_ERR_STATE
     assert h.fs.fs_batch_destroy(b) == 0
     assert h.fs.fs_ctx_destroy(other) == 0 and h.lib.host_used() < used
+
+
+def case_batches_go_on_other_threads(h):
+    """As a collector may have it: batches of a context are destroyed on another thread than the one that
+    works with the context, as before contexts knew their batches."""
+    used = h.lib.host_used()
+    made, errors = queue.SimpleQueue(), []
+
+    def destroy():
+        while (b := made.get()) is not None:
+            errors.append(h.fs.fs_batch_destroy(b))
+
+    threads = [threading.Thread(target=destroy) for _ in range(3)]
+    for t in threads:
+        t.start()
+    for _ in range(6000):
+        rc, b = h.batch()
+        assert rc == 0
+        made.put(b)
+        h.keep.clear()
+        h.kernels()
+    for _ in threads:
+        made.put(None)
+    for t in threads:
+        t.join()
+    assert errors == [0] * 6000 and h.lib.host_used() == used
+    assert h.fs.fs_ctx_destroy(h.ctx) == 0
 
 
 CASES = [c[5:] for c in dir() if c.startswith("case_")]
